@@ -1,8 +1,8 @@
 // Error measurement (Appendix E.2: relative error against an fp64 product)
 // and the standalone e4m3 codec.
 //
-// reference_f64_kernel: C_ref = A B in binary64 from fp32 operands; LDS-tiled,
-//   64 x 64 outputs per workgroup, 4 x 4 per thread, K steps of 16.
+// reference_f64_kernel: C_ref = A B in binary64 from fp32 operands, on the
+//   fp64 matrix cores.
 //   Measurement infrastructure: not on the timed path.
 // error partials / totals: per product, sum (C - C_ref)^2 and sum C_ref^2 in
 //   binary64 by a fixed grid of workgroups (each a fixed-order strided sum and
@@ -21,53 +21,102 @@ namespace fmm {
 
 namespace {
 
-constexpr int RT = 64, RK = 16;
+// C_ref on the fp64 matrix cores (v_mfma_f64_16x16x4_f64: lane l holds A row
+// l % 16 and B column l % 16 at contracted position l / 16; register e of the
+// result is row 4 e + l / 16, column l % 16).
+//
+// A workgroup of 2 x 2 waves owns a 64 x 64 tile, each wave TI x TI MFMA
+// tiles, so one 4-byte LDS read a lane feeds TI matrix instructions of 64
+// cycles.  The operands are staged in fp32, double-buffered in steps of 16
+// positions (a row of A every 20 floats and a position of B every 80, so that
+// the 16 x 4 reads fall on distinct banks), and widened on the way to the
+// matrix core, which is exact.  Bound by the fp64 matrix rate: 59.9 TFLOP/s at
+// 8192^3 (18.4 ms) and 58.6 at 4096^3, where the vendor library's fp64 product
+// reaches 61.9; an LDS-tiled fma kernel (64 x 64, 4 x 4
+// per thread) took 32.7 and 4.23 ms, and 441 us for two 2048 x 1024 x 1536
+// products (now 239).
+// 128 x 128 tiles (4 x 4 MFMA tiles a wave): 53.9 and 53.7, and 1.4 to 3 times
+// slower where they are too few to fill the chip; steps of 32: the same.
+constexpr int TI = 2, RT = 32 * TI, RK = 16;
 
-__global__ __launch_bounds__(256) void reference_f64_kernel(const float *__restrict__ A,
-                                                            const float *__restrict__ B,
-                                                            double *__restrict__ C, int64_t M,
-                                                            int64_t K, int64_t N, int64_t tiles_n) {
-  __shared__ double la[RK][RT + 1];
-  __shared__ double lb[RK][RT + 1];
-  const int t = threadIdx.x;
+typedef double v4d __attribute__((ext_vector_type(4)));
+
+__global__ __launch_bounds__(256, 4) void reference_f64_kernel(const float *__restrict__ A,
+                                                               const float *__restrict__ B,
+                                                               double *__restrict__ C, int64_t M,
+                                                               int64_t K, int64_t N, int tiles_n) {
+  constexpr int SA = RK + 4, SB = RT + 16;
+  constexpr int NA = RT * RK / 256, NSTEP_B = 256 / RT;   // loads per thread and side; B positions per pass
+  __shared__ float la[2][RT * SA], lb[2][RK * SB];
+  const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
+  const int wm = (wave >> 1) * 16 * TI, wn = (wave & 1) * 16 * TI;
+  const int c16 = lane & 15, q4 = lane >> 4;
   const int64_t bt = blockIdx.z;
-  const int64_t m0 = (blockIdx.x / tiles_n) * RT, n0 = (blockIdx.x % tiles_n) * RT;
-  const float *Ab = A + bt * M * K;
-  const float *Bb = B + bt * K * N;
-  const int tx = t % 16, ty = t / 16;   // 4 x 4 outputs at rows ty + 16 i, cols tx + 16 j
-  double acc[4][4] = {};
-  for (int64_t k0 = 0; k0 < K; k0 += RK) {
-    // A tile: 64 rows x 16 k; B tile: 16 k x 64 cols (1024 elements each)
-    for (int e = t; e < RT * RK; e += 256) {
-      const int r = e / RK, kk = e % RK;
-      const int64_t gm = m0 + r, gk = k0 + kk;
-      la[kk][r] = (gm < M && gk < K) ? (double)Ab[gm * K + gk] : 0.0;
-      const int kb = e / RT, c = e % RT;
-      const int64_t gk2 = k0 + kb, gn = n0 + c;
-      lb[kb][c] = (gk2 < K && gn < N) ? (double)Bb[gk2 * N + gn] : 0.0;
+  const int64_t m0 = (int64_t)(blockIdx.x / tiles_n) * RT, n0 = (int64_t)(blockIdx.x % tiles_n) * RT;
+  // rows of A and columns of B past the end repeat the last one (their
+  // outputs are not stored); positions past K read as zero
+  const int ak = t % RK, ar = t / RK, bc = t % RT, bk = t / RT;
+  const float *Ab = A + bt * M * K, *Bb = B + bt * K * N + min(n0 + bc, N - 1);
+  float sa[NA], sb[NA];
+  auto load = [&](int64_t k0) {
+    const bool whole = k0 + RK <= K;
+#pragma unroll
+    for (int i = 0; i < NA; ++i) {
+      const int64_t row = min(m0 + ar + (256 / RK) * i, M - 1);
+      sa[i] = whole || k0 + ak < K ? Ab[row * K + k0 + ak] : 0.0f;
+      const int64_t kb = k0 + bk + NSTEP_B * i;
+      sb[i] = whole || kb < K ? Bb[kb * N] : 0.0f;
     }
-    __syncthreads();
+  };
+  auto store = [&](int buf) {
 #pragma unroll
-    for (int kk = 0; kk < RK; ++kk) {
-      double a[4], b[4];
-#pragma unroll
-      for (int i = 0; i < 4; ++i) a[i] = la[kk][ty + 16 * i];
-#pragma unroll
-      for (int j = 0; j < 4; ++j) b[j] = lb[kk][tx + 16 * j];
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) acc[i][j] = fma(a[i], b[j], acc[i][j]);
+    for (int i = 0; i < NA; ++i) {
+      la[buf][(ar + (256 / RK) * i) * SA + ak] = sa[i];
+      lb[buf][(bk + NSTEP_B * i) * SB + bc] = sb[i];
     }
+  };
+  v4d acc[TI][TI];
+#pragma unroll
+  for (int i = 0; i < TI; ++i)
+#pragma unroll
+    for (int j = 0; j < TI; ++j) acc[i][j] = (v4d){0.0, 0.0, 0.0, 0.0};
+  if (K > 0) {
+    load(0);
+    store(0);
+  }
+  __syncthreads();
+  int buf = 0;
+  for (int64_t k0 = 0; k0 < K; k0 += RK, buf ^= 1) {
+    const bool more = k0 + RK < K;
+    if (more) load(k0 + RK);
+    const float *pa = la[buf] + (wm + c16) * SA + q4, *pb = lb[buf] + q4 * SB + wn + c16;
+#pragma unroll
+    for (int kk = 0; kk < RK; kk += 4) {
+      double a[TI], b[TI];
+#pragma unroll
+      for (int i = 0; i < TI; ++i) a[i] = (double)pa[16 * i * SA + kk];
+#pragma unroll
+      for (int j = 0; j < TI; ++j) b[j] = (double)pb[kk * SB + 16 * j];
+#pragma unroll
+      for (int i = 0; i < TI; ++i)
+#pragma unroll
+        for (int j = 0; j < TI; ++j)
+          acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[i], b[j], acc[i][j], 0, 0, 0);
+    }
+    // (the other buffer was last read before the barrier that ended the previous step)
+    if (more) store(buf ^ 1);
     __syncthreads();
   }
+  double *Cb = C + bt * M * N;
 #pragma unroll
-  for (int i = 0; i < 4; ++i)
+  for (int i = 0; i < TI; ++i)
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int64_t gm = m0 + ty + 16 * i, gn = n0 + tx + 16 * j;
-      if (gm < M && gn < N) C[bt * M * N + gm * N + gn] = acc[i][j];
-    }
+    for (int j = 0; j < TI; ++j)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const int64_t gm = m0 + wm + 16 * i + 4 * e + q4, gn = n0 + wn + 16 * j + c16;
+        if (gm < M && gn < N) Cb[gm * N + gn] = acc[i][j][e];
+      }
 }
 
 constexpr int kRedThreads = 256;
@@ -173,7 +222,7 @@ int launch_reference_f64(int64_t batch, int64_t M, int64_t K, int64_t N, const f
   hipStream_t st = reinterpret_cast<hipStream_t>(stream);
   const int64_t tm = (M + RT - 1) / RT, tn = (N + RT - 1) / RT;
   hipLaunchKernelGGL(reference_f64_kernel, dim3((unsigned)(tm * tn), 1, (unsigned)batch), dim3(256),
-                     0, st, A, B, Cref, M, K, N, tn);
+                     0, st, A, B, Cref, M, K, N, (int)tn);
   return hipGetLastError();
 }
 

@@ -1,0 +1,27 @@
+"""The error measurement at the sizes where its kernels can go wrong: the fp64
+reference at the edges of its 64 x 64 tiles and 16-position steps."""
+import numpy as np
+import pytest
+
+import fmm_inputs as gen
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("shape", [
+    (1, 1, 1, 1), (1, 64, 16, 64), (2, 63, 15, 65), (1, 65, 17, 63), (3, 130, 33, 70), (1, 2, 200, 129),
+    (2, 66, 0, 62),          # nothing to contract: zeros
+    (65, 16, 48, 80),
+])
+def test_reference_tile_edges(shape):
+    """Against numpy's binary64 product.  Both sum K products that binary64
+    holds exactly (24-bit factors) with at most K roundings each, so an element
+    differs by at most 2 K 2^-53 sum |a| |b|."""
+    import torch
+    from paper_2609_26077_amd.runner import reference_f64
+    b, M, K, N = shape
+    A, B = gen.operands("gaussian", b, M, K, N, seed=5, cfg=1)
+    C = reference_f64(torch.from_numpy(A).cuda(), torch.from_numpy(B).cuda()).cpu().numpy()
+    A64, B64 = A.astype(np.float64), B.astype(np.float64)
+    bound = 2 * K * 2.0 ** -53 * (np.abs(A64) @ np.abs(B64))
+    assert np.all(np.abs(C - A64 @ B64) <= bound)
