@@ -789,13 +789,40 @@ hipError_t launch_side(const Problem &pb, const float *src, const SideTab &cf,
 
 // ---- operand-side rounding energy (MODE 3) ----------------------------------
 
+// One side's noise partials: slot ((bt * tiles + tile) * waves + wave) * T + r
+// holds term r's sums over the rows of that wave, written for the terms the
+// wave works on (r mod step = wave / wpt; MODE 3 of encode16_kernel).
+struct NoiseSide {
+  const double *partial;
+  int64_t tiles;
+  int waves, wpt, step;
+};
+
+// tiles of one product's side, and waves per workgroup, of MODE 3
+template <int SIDE>
+int64_t noise_tiles(const Problem &pb) {
+  const int64_t rows = SIDE == 0 ? pb.mp : pb.np;
+  const int64_t tr = pb.depth == 1 ? Tile<1, 16, SIDE>::TR : Tile<2, 16, SIDE>::TR;
+  return ((pb.kp + kTL - 1) / kTL) * ((rows + tr - 1) / tr);
+}
+template <int SIDE>
+int noise_waves(const Problem &pb) {
+  return (pb.depth == 1 ? Tile<1, 16, SIDE>::threads : Tile<2, 16, SIDE>::threads) / 64;
+}
 template <int SIDE>
 int64_t noise_slots(const Problem &pb) {
-  const int64_t rows = SIDE == 0 ? pb.mp : pb.np;
-  const int64_t tiles = ((pb.kp + kTL - 1) / kTL) * ((rows + (pb.depth == 1 ? Tile<1, 16, SIDE>::TR : Tile<2, 16, SIDE>::TR) - 1) /
-                                                    (pb.depth == 1 ? Tile<1, 16, SIDE>::TR : Tile<2, 16, SIDE>::TR));
-  const int64_t waves = (pb.depth == 1 ? Tile<1, 16, SIDE>::threads : Tile<2, 16, SIDE>::threads) / 64;
-  return pb.batch * tiles * waves * pb.T;
+  return pb.batch * noise_tiles<SIDE>(pb) * noise_waves<SIDE>(pb) * pb.T;
+}
+template <int SIDE>
+NoiseSide noise_side(const Problem &pb, const double *partial) {
+  NoiseSide s;
+  s.partial = partial;
+  s.tiles = noise_tiles<SIDE>(pb);
+  s.waves = noise_waves<SIDE>(pb);
+  // waves that share a term's rows (8 each), as encode16_kernel's WPT
+  s.wpt = (pb.depth == 1 ? Tile<1, 16, SIDE>::TR : Tile<2, 16, SIDE>::TR) / 8;
+  s.step = s.waves / s.wpt;
+  return s;
 }
 
 template <int SIDE, int DEPTH>
@@ -814,17 +841,40 @@ hipError_t launch_noise_side(const Problem &pb, const float *src, const SideTab 
   return hipErrorInvalidValue;
 }
 
-// out[(bt * 2 + side) * T + r][q] = sum over the side's tiles and waves of
-// partial[((bt * tiles + tile) * waves + wave) * T + r][q], in that order.
-__global__ __launch_bounds__(256) void noise_reduce_kernel(const double *__restrict__ partial, double *__restrict__ out,
-                                                           int64_t batch, int64_t T, int64_t per_bt, int side) {
-  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;     // (bt, r, q)
-  if (i >= batch * T * 2) return;
-  const int64_t q = i & 1, r = (i >> 1) % T, bt = (i >> 1) / T;
-  double s = 0.0;
-  const double *p = partial + (bt * per_bt * T + r) * 2 + q;
-  for (int64_t k = 0; k < per_bt; ++k) s += p[k * T * 2];
-  out[((bt * 2 + side) * T + r) * 2 + q] = s;
+// out[(bt * 2 + side) * T + r][q]: one workgroup per (term, side, product)
+// sums the term's slots, thread t taking slots t, t + 256, .. in that order,
+// then the lanes by a fixed butterfly and the four waves in order.  (A thread
+// per output walking every slot, and a pass that cleared the slots nobody
+// writes, took 448 us for two 2048 x 1024 x 1536 products; this takes 3.8.)
+__global__ __launch_bounds__(256) void noise_reduce_kernel(NoiseSide a, NoiseSide b, double *__restrict__ out, int64_t T) {
+  const int t = threadIdx.x;
+  const int64_t r = blockIdx.x, side = blockIdx.y, bt = blockIdx.z;
+  const NoiseSide s = side == 0 ? a : b;
+  const int w0 = s.wpt * (int)(r % s.step);
+  const int64_t n = s.tiles * s.wpt;
+  double e2 = 0.0, x2 = 0.0;
+  for (int64_t k = t; k < n; k += 256) {
+    const int64_t tile = k / s.wpt;
+    const int64_t slot = ((bt * s.tiles + tile) * s.waves + w0 + (k - tile * s.wpt)) * T + r;
+    e2 += s.partial[2 * slot];
+    x2 += s.partial[2 * slot + 1];
+  }
+#pragma unroll
+  for (int sh = 32; sh >= 1; sh >>= 1) {
+    e2 += __shfl_xor(e2, sh, 64);
+    x2 += __shfl_xor(x2, sh, 64);
+  }
+  __shared__ double se[4], sx[4];
+  if ((t & 63) == 0) {
+    se[t >> 6] = e2;
+    sx[t >> 6] = x2;
+  }
+  __syncthreads();
+  if (t == 0) {
+    double *o = out + ((bt * 2 + side) * T + r) * 2;
+    o[0] = ((se[0] + se[1]) + se[2]) + se[3];
+    o[1] = ((sx[0] + sx[1]) + sx[2]) + sx[3];
+  }
 }
 
 }  // namespace
@@ -840,12 +890,7 @@ int launch_encode_noise(const Problem &pb, const DeviceTables &tab, const float 
   if (pb.batch == 0 || pb.T == 0) return hipSuccess;
   double *pa = reinterpret_cast<double *>(scratch);
   double *pbp = pa + noise_slots<0>(pb) * 2;
-  const int64_t n = (noise_slots<0>(pb) + noise_slots<1>(pb)) * 2;
-  // slots a wave does not own (depth 2 deals terms out over the waves) must read as zero
-  hipLaunchKernelGGL(zero_u32_kernel, dim3((unsigned)std::min<int64_t>((2 * n + 255) / 256, 4096)), dim3(256), 0, st,
-                     reinterpret_cast<uint32_t *>(scratch), 2 * n);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
+  hipError_t e;
   if (pb.M > 0 && pb.K > 0) {
     e = pb.depth == 1 ? launch_noise_side<0, 1>(pb, A, a_tab(tab), ws + wl.a_codes, ws + wl.a_scales, pa, st)
                       : launch_noise_side<0, 2>(pb, A, a_tab(tab), ws + wl.a_codes, ws + wl.a_scales, pa, st);
@@ -856,10 +901,8 @@ int launch_encode_noise(const Problem &pb, const DeviceTables &tab, const float 
                       : launch_noise_side<1, 2>(pb, B, b_tab(tab), ws + wl.b_codes, ws + wl.b_scales, pbp, st);
     if (e != hipSuccess) return e;
   }
-  const int64_t tot = pb.batch * pb.T * 2;
-  const dim3 g((unsigned)((tot + 255) / 256));
-  hipLaunchKernelGGL(noise_reduce_kernel, g, dim3(256), 0, st, pa, out, pb.batch, pb.T, noise_slots<0>(pb) / (pb.batch * pb.T), 0);
-  hipLaunchKernelGGL(noise_reduce_kernel, g, dim3(256), 0, st, pbp, out, pb.batch, pb.T, noise_slots<1>(pb) / (pb.batch * pb.T), 1);
+  hipLaunchKernelGGL(noise_reduce_kernel, dim3((unsigned)pb.T, 2, (unsigned)pb.batch), dim3(256), 0, st,
+                     noise_side<0>(pb, pa), noise_side<1>(pb, pbp), out, pb.T);
   return hipGetLastError();
 }
 

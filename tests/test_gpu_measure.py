@@ -1,9 +1,12 @@
 """The error measurement at the sizes where its kernels can go wrong: the fp64
-reference at the edges of its 64 x 64 tiles and 16-position steps."""
+reference at the edges of its 64 x 64 tiles and 16-position steps, and the
+operand-noise reduction where a term has fewer and more partials than one
+workgroup has threads."""
 import numpy as np
 import pytest
 
 import fmm_inputs as gen
+from tests.test_gpu_noise import gpu_noise, oracle_noise
 
 pytestmark = pytest.mark.gpu
 
@@ -25,3 +28,19 @@ def test_reference_tile_edges(shape):
     A64, B64 = A.astype(np.float64), B.astype(np.float64)
     bound = 2 * K * 2.0 ** -53 * (np.abs(A64) @ np.abs(B64))
     assert np.all(np.abs(C - A64 @ B64) <= bound)
+
+
+@pytest.mark.parametrize("case", [
+    (1, 2, 32, 2, 1),           # one partial a term
+    (1, 1040, 1024, 130, 1),    # 65 row tiles x 4: 260 partials on the A side
+    (2, 516, 1280, 36, 2),      # two levels, ragged tiles
+])
+def test_noise_partials(case):
+    """The sums of non-negative terms, to the relative error of as many
+    binary64 additions (well inside 1e-12)."""
+    b, M, K, N, depth = case
+    bs = 16
+    A, B, _, _, _, g = gpu_noise("strassen", "gaussian", b, M, K, N, depth, bs, 1)
+    for i in range(b):
+        o = oracle_noise(A[i], B[i], "strassen", depth, bs, 1)
+        assert np.allclose(g[i], o, rtol=1e-12, atol=0)
