@@ -20,8 +20,8 @@ COMMON = ["-O3", "-std=c++17", "-fPIC", "-ffp-contract=off", "-Wall",
           "-Wno-unused-function", "-Wno-unused-variable"]
 DEVICE = ["--offload-arch=gfx950", "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
           "-munsafe-fp-atomics"]
-# the 128 x 128 kernels keep the MFMA accumulator in VGPRs (the AGPRs hold the
-# W-combine quadrants); the 256 x 256 kernel keeps its 256 accumulators in AGPRs
+# the 128 x 128 kernels keep the MFMA accumulators in VGPRs, beside the W-combine
+# quadrants they are added to; the 256 x 256 kernel keeps its 256 accumulators in AGPRs
 PER_FILE = {"kernels_gemm.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"]}
 
 

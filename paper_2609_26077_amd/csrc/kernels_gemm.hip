@@ -24,7 +24,7 @@
 // Exact-dot paths (FMM_FLAG_EXACT_DOT, fp32 scales or block 16): the codes are
 // converted exactly to bf16 and fed to v_mfma_f32_32x32x16_bf16 (lane (r, h)
 // holds row r, elements [8h, 8h+8); 23 retained bits).  With E8M0 scales on
-// the tile layout (gemm_dq8_kernel) each code's conversion applies its block's
+// the tile layout (gemm_tile128_kernel) each code's conversion applies its block's
 // power of two; otherwise (gemm_promote_kernel) the codes convert at scale 1,
 // each block's products are summed in a temporary and scaled by sA * sB in
 // fp32 -- in both, the products of the dequantized operands accumulated in fp32.
@@ -271,128 +271,14 @@ __global__ __launch_bounds__(kThreads, 1) void gemm_mx_kernel(GemmArgs g) {
 
 
 // ---------------------------------------------------------------------------
-// Fast MX path for tile-aligned shapes (m', n' and k' multiples of 128), whose
-// codes and scales the encoder writes in the 128 x 128 tile layout.
-//
-// One workgroup of four waves owns a 128 x 128 tile of the m' x n' grid; each
-// wave a 64 x 64 quarter as 2 x 2 MFMA tiles of 32 x 32.  The codes and E8M0
-// scales of each 128-byte K step go from HBM straight into LDS
-// (global_load_lds: no staging registers) through a four-slot ring; each wave
-// issues exactly nine such transfers per step (four 1 KB of A codes, four of
-// B codes, one 256 B of scales), all straight copies of the tile images, and
-// waits for them with an explicit vmcnt.
-// While the MFMAs of step s run on fragments already in registers, the
-// fragments of step s + 1 are read from LDS into a second register set and the
-// transfers of steps s + 2 and s + 3 are in flight.  LDS code rows are 128
-// bytes; 16-byte chunk c of row r is stored at c ^ (r & 7) ^ ((r >> 3) & 1),
-// which keeps every 16-lane group of a fragment read on distinct banks.
-//
-// The quadrant accumulators of the fused W-combine live in AGPRs for the
-// whole kernel (the four 64 x 64 sets fill the 256 accumulation registers),
-// leaving the architectural VGPRs to the MFMA accumulator, the two fragment
-// sets and addressing; they are touched only through the helpers below, eight
-// at a time at a term end.  The decoder weights are copied to LDS once, so the
-// term-end combine never waits on vector memory (which would drain the
-// transfer ring).
+// 128 x 128 tiles: see gemm_tile128_kernel
 // ---------------------------------------------------------------------------
 constexpr int FBK = 128;
-constexpr int kSlot = 2 * BM * FBK + 2 * BM * 4;   // codes A, B + scale words A, B
 constexpr int kSlots = 4;
 
 using dma::copy16;
 using dma::copy4;
 using dma::wait_vmcnt;
-
-__device__ __forceinline__ void agpr_zero(float &q) {
-  asm volatile("v_accvgpr_write_b32 %0, 0" : "=a"(q));
-}
-__device__ __forceinline__ void agpr_fma(float &q, float w, float p) {
-  float t;
-  asm volatile(
-      "v_accvgpr_read_b32 %0, %1\n\t"
-      "v_fmac_f32_e32 %0, %2, %3\n\t"
-      "v_accvgpr_write_b32 %1, %0"
-      : "=&v"(t), "+a"(q)
-      : "s"(w), "v"(p));
-}
-// eight of the above at once, on eight temporaries, so the reads, the
-// multiply-adds and the writes each issue back to back
-__device__ __forceinline__ void agpr_fma8(float *q, float w, const float *p) {
-  float t0, t1, t2, t3, t4, t5, t6, t7;
-  asm volatile(
-      "v_accvgpr_read_b32 %0, %8\n\tv_accvgpr_read_b32 %1, %9\n\t"
-      "v_accvgpr_read_b32 %2, %10\n\tv_accvgpr_read_b32 %3, %11\n\t"
-      "v_accvgpr_read_b32 %4, %12\n\tv_accvgpr_read_b32 %5, %13\n\t"
-      "v_accvgpr_read_b32 %6, %14\n\tv_accvgpr_read_b32 %7, %15\n\t"
-      "v_fmac_f32_e32 %0, %16, %17\n\tv_fmac_f32_e32 %1, %16, %18\n\t"
-      "v_fmac_f32_e32 %2, %16, %19\n\tv_fmac_f32_e32 %3, %16, %20\n\t"
-      "v_fmac_f32_e32 %4, %16, %21\n\tv_fmac_f32_e32 %5, %16, %22\n\t"
-      "v_fmac_f32_e32 %6, %16, %23\n\tv_fmac_f32_e32 %7, %16, %24\n\t"
-      "v_accvgpr_write_b32 %8, %0\n\tv_accvgpr_write_b32 %9, %1\n\t"
-      "v_accvgpr_write_b32 %10, %2\n\tv_accvgpr_write_b32 %11, %3\n\t"
-      "v_accvgpr_write_b32 %12, %4\n\tv_accvgpr_write_b32 %13, %5\n\t"
-      "v_accvgpr_write_b32 %14, %6\n\tv_accvgpr_write_b32 %15, %7"
-      : "=&v"(t0), "=&v"(t1), "=&v"(t2), "=&v"(t3), "=&v"(t4), "=&v"(t5), "=&v"(t6), "=&v"(t7),
-        "+a"(q[0]), "+a"(q[1]), "+a"(q[2]), "+a"(q[3]), "+a"(q[4]), "+a"(q[5]), "+a"(q[6]), "+a"(q[7])
-      : "s"(w), "v"(p[0]), "v"(p[1]), "v"(p[2]), "v"(p[3]), "v"(p[4]), "v"(p[5]), "v"(p[6]), "v"(p[7]));
-}
-__device__ __forceinline__ float agpr_read(const float &q) {
-  float v;
-  asm volatile("v_accvgpr_read_b32 %0, %1" : "=v"(v) : "a"(q));
-  return v;
-}
-
-// XCD-aware tile order: workgroups are dispatched round-robin over the eight
-// XCDs, so consecutive workgroups of one XCD (bid, bid + 8, ...) are given a
-// contiguous range of tiles, walked in groups of eight tile-rows so that the
-// workgroups resident on an XCD share A rows and B columns in its L2.
-__device__ __forceinline__ void tile_of(int bid, int tiles_m, int tiles_n, int &tm, int &tn) {
-  const int ntiles = tiles_m * tiles_n;
-  int id = bid;
-  if ((ntiles & 7) == 0) id = (bid & 7) * (ntiles >> 3) + (bid >> 3);
-  constexpr int GM = 8;
-  const int per_group = GM * tiles_n;
-  const int group = id / per_group;
-  const int first_m = group * GM;
-  const int gm = min(tiles_m - first_m, GM);
-  const int in = id - group * per_group;
-  tm = first_m + in % gm;
-  tn = in / gm;
-}
-
-// The (tile, outer term, batch) item of this workgroup.  Grids whose tile
-// count is not a multiple of eight (small batched products: 2 x 2 tiles of a
-// 256 x 256 sub-product) would spread the tiles of one item over four XCDs,
-// each fetching the item's codes into its own L2; there the linear dispatch
-// index L (x fastest) is remapped, as for the large-tile kernel, so that XCD
-// L mod 8 takes a contiguous range of items and all tiles of each (1024
-// products of 512^3: 0.64 -> 0.54 ms).  Grids of fewer than 2048 workgroups
-// (eight rounds of the 256 the chip holds) keep the plain order, which
-// measured slightly faster there.
-__device__ __forceinline__ void item_of(int tiles_m, int tiles_n, int &tm, int &tn, int64_t &ro, int64_t &bt) {
-  const int ntiles = tiles_m * tiles_n;
-  const int64_t total = (int64_t)ntiles * gridDim.y * gridDim.z;
-  if ((ntiles & 7) == 0 || (total & 7) != 0 || total < 2048) {
-    tile_of(blockIdx.x, tiles_m, tiles_n, tm, tn);
-    ro = blockIdx.y;
-    bt = blockIdx.z;
-    return;
-  }
-  const int64_t L = blockIdx.x + (int64_t)ntiles * (blockIdx.y + (int64_t)gridDim.y * blockIdx.z);
-  const int64_t id = (L & 7) * (total >> 3) + (L >> 3);
-  const int64_t item = id / ntiles;
-  tile_of((int)(id - item * ntiles), tiles_m, tiles_n, tm, tn);
-  ro = item % gridDim.y;
-  bt = item / gridDim.y;
-}
-
-// Operands of one K step for one wave: fragments [substep s][tile i] and,
-// for each of its A and B row tiles, the E8M0 scale bytes of the lane's two
-// blocks (byte s: substep s).
-struct MxFrags {
-  v8i a[2][2], b[2][2];
-  int sa[2], sb[2];
-};
 
 // codes in dwords d, d + 1 of a fragment, times the power of two whose
 // exponent field `s` carries, as eight bf16 (exact: the dequantized values)
@@ -416,188 +302,25 @@ __device__ __forceinline__ float e8m0_at(int w, int i) {
   return __uint_as_float(i == 3 ? (uint32_t)w >> 1 : (uint32_t)w << (23 - 8 * i));
 }
 
-// The fp8 matrix cores with the E8M0 scales applied by the scaled MFMA.
-template <int BS>
-__global__ __launch_bounds__(kThreads, 1) void gemm_mx_fast_kernel(GemmArgs g, int tiles_m) {
-  __shared__ uint4 lds_raw[kSlots * kSlot / 16];
-  __shared__ float lds_w[4 * kMaxRank];
-  uint8_t *lds = reinterpret_cast<uint8_t *>(lds_raw);
-  const uint32_t lds_base = dma::lds_addr(lds_raw);
-  const int t = threadIdx.x;
-  const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
-  const int lane = t & 63;
-  const int wm = wave >> 1, wn = wave & 1;
-  const int r32 = lane & 31, h = lane >> 5;
-  int tm, tn;
-  int64_t ro, bt;
-  item_of(tiles_m, g.tiles_n, tm, tn, ro, bt);
-  const int64_t pm0 = (int64_t)tm * BM, pn0 = (int64_t)tn * BN;
-  const uint32_t kp = (uint32_t)g.kp, kblocks = (uint32_t)g.kblocks;
-  const int nk = (int)(g.kp / FBK);
-  const int total = g.R * nk;
-  const int wrow_a = wm * 64, wrow_b = wn * 64;
-  if (t == 0) {   // uniform loads of the zero-padded table; read only after the first barrier
-#pragma unroll
-    for (int i = 0; i < 4 * kMaxRank; ++i) lds_w[i] = g.w[i];
-  }
-
-  // Codes and scales arrive tiled (the 128-row x 128-byte tile image and 4
-  // scale bytes per tile row and step), so every transfer is a straight copy:
-  // lane l moves bytes 16 l .. 16 l + 15 (codes) or 4 l .. 4 l + 3 (scales).
-  // Scales: waves 0/1 move A tile rows 64 w .., waves 2/3 B tile rows 64 (w - 2) ..
-  const bool scale_is_b = wave >= 2;
-  const int64_t kt = g.kp / FBK;                           // 128-byte steps per row tile
-
-  auto issue = [&](int step) {
-    const int ri = step / nk, ks = step - ri * nk;
-    const int64_t r = ro * g.R + ri;
-    const int64_t ta = ((bt * g.T + r) * (g.mp / BM) + tm) * kt + ks;   // tile index, A
-    const int64_t tb = ((bt * g.T + r) * (g.np / BN) + tn) * kt + ks;
-    const uint8_t *xa = g.xa + ta * (BM * FBK);
-    const uint8_t *xb = g.xb + tb * (BN * FBK);
-    const uint32_t m0 = lds_base + (uint32_t)(step & (kSlots - 1)) * kSlot;
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int region = wave * 4 + j;                     // tile rows 8 region .. + 7
-      copy16(16u * (uint32_t)lane, xa + region * 1024, m0 + region * 1024);
-      copy16(16u * (uint32_t)lane, xb + region * 1024, m0 + BM * FBK + region * 1024);
-    }
-    const uint8_t *sbase = scale_is_b ? g.sb + tb * (BN * 4) : g.sa + ta * (BM * 4);
-    copy4(4u * (uint32_t)lane + (wave & 1) * 256u, sbase,
-          m0 + 2 * BM * FBK + (scale_is_b ? BM * 4 : 0) + (wave & 1) * 256);
-  };
-
-  // LDS -> registers for one step (slot step % 4; any step index reads in bounds).
-  // Scale record of a row: blocks (0, 2, 1, 3) at block 32, so lane (r, h) reads
-  // the 16-bit pair at byte 2h: byte 0 = block h (substep 0), byte 1 = block 2 + h.
-  auto load = [&](int step, MxFrags &f) {
-    const uint8_t *la = lds + (step & (kSlots - 1)) * kSlot;
-    const uint8_t *lb = la + BM * FBK;
-    const uint8_t *lsa = la + 2 * BM * FBK;
-    const uint8_t *lsb = lsa + BM * 4;
-#pragma unroll
-    for (int i = 0; i < 2; ++i) {
-      f.sa[i] = *reinterpret_cast<const uint16_t *>(lsa + 4 * (wrow_a + 32 * i + r32) + 2 * h);
-      f.sb[i] = *reinterpret_cast<const uint16_t *>(lsb + 4 * (wrow_b + 32 * i + r32) + 2 * h);
-    }
-#pragma unroll
-    for (int s = 0; s < 2; ++s)
-#pragma unroll
-      for (int i = 0; i < 2; ++i) {
-        f.a[s][i] = frag_mx(la, wrow_a + 32 * i + r32, s, h);
-        f.b[s][i] = frag_mx(lb, wrow_b + 32 * i + r32, s, h);
-      }
-  };
-
-  v16f acc[2][2];
-  float quad[4][2][2][16];
-#pragma unroll
-  for (int i = 0; i < 2; ++i)
-#pragma unroll
-    for (int j = 0; j < 2; ++j) {
-      acc[i][j] = (v16f){};
-#pragma unroll
-      for (int q = 0; q < 4; ++q)
-#pragma unroll
-        for (int e = 0; e < 16; ++e) agpr_zero(quad[q][i][j][e]);
-    }
-
-  // one step: wait for step + 1, start step + 3, read step + 1 into `nxt`
-  // while the MFMAs of `cur` (step) run, and at the end of a term fold P_r
-  // into the quadrants.  The scale bytes of `cur` are selected here, a step after
-  // their words were read, so no MFMA waits on a scale read.
-  auto body = [&](int step, MxFrags &cur, MxFrags &nxt) {
-    if (step + 1 < total) {
-      if (step + 2 < total) wait_vmcnt<9>(); else wait_vmcnt<0>();
-      __syncthreads();
-    }
-    if (step + 3 < total) issue(step + 3);
-    const int ks = step % nk;
-    load(step + 1, nxt);
-    {
-#define FMM_MFMA_SIJ(S, I, J)                                                                      \
-  acc[I][J] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(cur.a[S][I], cur.b[S][J], acc[I][J], 0, 0, \
-                                                              S, cur.sa[I], S, cur.sb[J])
-      FMM_MFMA_SIJ(0, 0, 0); FMM_MFMA_SIJ(0, 0, 1); FMM_MFMA_SIJ(0, 1, 0); FMM_MFMA_SIJ(0, 1, 1);
-      FMM_MFMA_SIJ(1, 0, 0); FMM_MFMA_SIJ(1, 0, 1); FMM_MFMA_SIJ(1, 1, 0); FMM_MFMA_SIJ(1, 1, 1);
-#undef FMM_MFMA_SIJ
-      // MFMA and LDS reads alternate: 1 MFMA, then 3 reads (20 reads over 7 gaps)
-#pragma unroll
-      for (int k = 0; k < 6; ++k) {
-        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-        __builtin_amdgcn_sched_group_barrier(0x100, 3, 0);
-      }
-      __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-      __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
-      __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-    }
-    if (ks + 1 == nk) {
-      const int ri = step / nk;
-      // end of term ri: quadrant q += w[ri][q] * P
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const float wq = __builtin_bit_cast(
-            float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, lds_w[4 * ri + q])));
-        if (wq != 0.0f) {
-#pragma unroll
-          for (int i = 0; i < 2; ++i)
-#pragma unroll
-            for (int j = 0; j < 2; ++j)
-#pragma unroll
-              for (int e = 0; e < 16; e += 8) {
-                float pv[8];
-#pragma unroll
-                for (int u = 0; u < 8; ++u) pv[u] = acc[i][j][e + u];
-                agpr_fma8(&quad[q][i][j][e], wq, pv);
-              }
-        }
-      }
-#pragma unroll
-      for (int i = 0; i < 2; ++i)
-#pragma unroll
-        for (int j = 0; j < 2; ++j) acc[i][j] = (v16f){};
-    }
-  };
-
-  // prologue: steps 0, 1, 2 in flight, step 0 read into registers
-  issue(0);
-  if (total > 1) issue(1);
-  if (total > 2) issue(2);
-  if (total > 2) wait_vmcnt<18>(); else if (total > 1) wait_vmcnt<9>(); else wait_vmcnt<0>();
-  __syncthreads();
-  MxFrags f0, f1;
-  load(0, f0);
-  for (int step = 0; step < total; step += 2) {
-    body(step, f0, f1);
-    if (step + 1 < total) body(step + 1, f1, f0);
-  }
-
-#pragma unroll
-  for (int q = 0; q < 4; ++q)
-#pragma unroll
-    for (int i = 0; i < 2; ++i)
-#pragma unroll
-      for (int j = 0; j < 2; ++j) {
-        v16f v;
-#pragma unroll
-        for (int e = 0; e < 16; ++e) v[e] = agpr_read(quad[q][i][j][e]);
-        store_tile(g, bt, ro, q, pm0 + wrow_a + 32 * i, pn0 + wrow_b + 32 * j, v);
-      }
-}
-
 // ---------------------------------------------------------------------------
-// Exact-dot fused sub-products on the 128 x 128 tile layout (E8M0 scales,
-// blocks 32 and 128), two waves per SIMD.
+// Fused sub-products on the 128 x 128 tile layout (E8M0 scales), two waves per
+// SIMD; on the fp8 matrix cores, or (EXACT) exact-dot.
 //
 // One persistent workgroup of eight waves per CU walks a list of (tile,
 // outer term, batch) items; its (item, term, K step) sequence is a single
 // transfer pipeline, so the codes of the next item are in flight while the
-// current one ends.  Each wave owns 64 rows x 32 columns of the 128 x 128
-// tile (two 32 x 32 MFMA tiles), which leaves room for its four W-combine
-// quadrants (128 floats a lane) in the architectural registers beside the
-// accumulators: a term-end combine is one multiply-add per nonzero weight and
-// element, and while one wave converts codes or combines, the other wave on
-// its SIMD keeps the matrix core busy.
+// current one ends.  The codes and E8M0 scales of each 128-byte K step go
+// from HBM straight into LDS (global_load_lds: no staging registers) through
+// a four-slot ring, all as straight copies of the tile images; a wave waits
+// for its own transfers with an explicit vmcnt.  Each wave owns 64 rows x 32
+// columns of the 128 x 128 tile (two 32 x 32 MFMA tiles), which leaves room
+// for its four W-combine quadrants (128 floats a lane) in the architectural
+// registers beside the accumulators: a term-end combine is one multiply-add
+// per nonzero weight and element, and while one wave converts codes or
+// combines, the other wave on its SIMD keeps the matrix core busy.  LDS code
+// rows are 128 bytes; 16-byte chunk c of row r is stored at
+// c ^ (r & 7) ^ ((r >> 3) & 1), which keeps every 16-lane group of a fragment
+// read on distinct banks.
 //
 // The MFMAs take the A fragment as their first operand, so a lane holds one
 // column of P and, in each register quadruple, four consecutive rows: one
@@ -606,8 +329,16 @@ __global__ __launch_bounds__(kThreads, 1) void gemm_mx_fast_kernel(GemmArgs g, i
 // bytes of each of 32 rows per 16-byte store instruction, measured 10% slower
 // on the batched 512^3 products).
 //
-// Transfers and fragments are those of gemm_mx_fast_kernel (the 128 x 128
-// tile images through a four-slot ring).  Each 64-byte substep runs as four
+// fp8: each 64-byte substep is one v_mfma_scale_f32_32x32x64_f8f6f4 per 32 x 32
+// tile, the lane (r, h) supplying the record bytes 2 h + s (block 2 s + h).
+// A four-wave form (64 x 64 per wave, the quadrants in AGPRs: one wave per
+// SIMD, three instructions per quadrant element and term end) took, against
+// this one (products alone, block 32): 100 products of 256^3 30.0 against
+// 15.9 us, 1024 of 512^3 547 against 376 us (HBM-bound: 5.5 TB/s), 64 of
+// 2048x1024x2048 709 against 545 us, 8192^3 at three levels 805 against 676,
+// one 256^3 27.0 against 13.8; nothing was faster.  C is bit-identical.
+//
+// Exact-dot: each 64-byte substep runs as four
 // v_mfma_f32_32x32x16_bf16 per tile pair on operands converted by
 // v_cvt_scalef32_pk_bf16_fp8 with the block's E8M0 scale as the scale
 // operand (the dequantized value, exact for every scale the rules produce),
@@ -615,12 +346,13 @@ __global__ __launch_bounds__(kThreads, 1) void gemm_mx_fast_kernel(GemmArgs g, i
 // contracted axis at fp32 grade.  Instruction t of substep s takes, in lane
 // half h, bytes 64 s + 32 (t >> 1) + 16 h + 8 (t & 1) .. + 7 of the row on
 // both operands, which lie in block 2 s + (t >> 1) at block 32 (record byte
-// 2 (t >> 1) + s, the record holding blocks 0, 2, 1, 3).  P_r starts from
-// zero at each term, and quadrant q of an item accumulates w[r_i][q] * P_r by
-// a fused multiply-add in ascending r_i.
+// 2 (t >> 1) + s, the record holding blocks 0, 2, 1, 3).
+//
+// P_r starts from zero at each term, and quadrant q of an item accumulates
+// w[r_i][q] * P_r by a fused multiply-add in ascending r_i.
 // Requires m', n', k' multiples of 128 (the layout's).
 // ---------------------------------------------------------------------------
-constexpr int kDqThreads = 512;
+constexpr int kTileThreads = 512;
 
 // s_barrier after this wave's LDS reads have completed; the transfers a wave
 // waits for are tracked by wait_vmcnt, and no global store needs to drain here
@@ -628,8 +360,8 @@ __device__ __forceinline__ void lds_barrier() {
   asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
 }
 
-template <int BS>
-__global__ __launch_bounds__(kDqThreads, 1) void gemm_dq8_kernel(GemmArgs g, int tiles_m, int nitems) {
+template <int BS, bool EXACT>
+__global__ __launch_bounds__(kTileThreads, 1) void gemm_tile128_kernel(GemmArgs g, int tiles_m, int nitems) {
   // scale record per row and step: 4 bytes (blocks 32, 128) or 8 (block 16)
   constexpr int REC = BS == 16 ? 8 : 4;
   constexpr int SLOT = 2 * BM * FBK + 2 * BM * REC;
@@ -766,17 +498,25 @@ __global__ __launch_bounds__(kDqThreads, 1) void gemm_dq8_kernel(GemmArgs g, int
     const uint4 hi = *reinterpret_cast<const uint4 *>(pb1);
     f.b = (v8i){(int)lo.x, (int)lo.y, (int)lo.z, (int)lo.w, (int)hi.x, (int)hi.y, (int)hi.z, (int)hi.w};
   };
-  // scales of one step: at blocks 32 and 128 the rows' whole records
-  // (blocks 0, 2, 1, 3 at block 32); at block 16 the word of the lane half,
-  // h = 0: blocks 0, 2, 4, 6, h = 1: blocks 1, 3, 5, 7 (instruction t of
-  // substep s reads block 4 s + 2 (t >> 1) + h)
-  const uint32_t lsa_off = 2 * BM * FBK + REC * (uint32_t)(wrow_a + r32) + (BS == 16 ? 4 * h : 0);
-  const uint32_t lsb_off = 2 * BM * FBK + BM * REC + REC * (uint32_t)(wrow_b + r32) + (BS == 16 ? 4 * h : 0);
+  // scales of one step: fp8, the lane half's two bytes of each row's record
+  // (blocks h and 2 + h at block 32); exact-dot, at blocks 32 and 128 the rows'
+  // whole records (blocks 0, 2, 1, 3 at block 32), at block 16 the word of the
+  // lane half, h = 0: blocks 0, 2, 4, 6, h = 1: blocks 1, 3, 5, 7 (instruction t
+  // of substep s reads block 4 s + 2 (t >> 1) + h)
+  constexpr int SCH = !EXACT ? 2 : BS == 16 ? 4 : 0;
+  const uint32_t lsa_off = 2 * BM * FBK + REC * (uint32_t)(wrow_a + r32) + SCH * h;
+  const uint32_t lsb_off = 2 * BM * FBK + BM * REC + REC * (uint32_t)(wrow_b + r32) + SCH * h;
   auto read_scales = [&](int64_t step, int (&sa)[2], int &sb) {
     const uint8_t *slot = lds + (step & (kSlots - 1)) * SLOT;
-    sa[0] = *reinterpret_cast<const int *>(slot + lsa_off);
-    sa[1] = *reinterpret_cast<const int *>(slot + lsa_off + 32 * REC);
-    sb = *reinterpret_cast<const int *>(slot + lsb_off);
+    if constexpr (EXACT) {
+      sa[0] = *reinterpret_cast<const int *>(slot + lsa_off);
+      sa[1] = *reinterpret_cast<const int *>(slot + lsa_off + 32 * REC);
+      sb = *reinterpret_cast<const int *>(slot + lsb_off);
+    } else {
+      sa[0] = *reinterpret_cast<const uint16_t *>(slot + lsa_off);
+      sa[1] = *reinterpret_cast<const uint16_t *>(slot + lsa_off + 32 * REC);
+      sb = *reinterpret_cast<const uint16_t *>(slot + lsb_off);
+    }
   };
 
   v16f acc[2];
@@ -793,6 +533,12 @@ __global__ __launch_bounds__(kDqThreads, 1) void gemm_dq8_kernel(GemmArgs g, int
   // the MFMAs of substep SS (the A fragment as the first operand)
   auto mfma_sub = [&](auto ssc, const Frag &f, const int (&sa)[2], int sb) {
     constexpr int SS = decltype(ssc)::value;
+    if constexpr (!EXACT) {
+#pragma unroll
+      for (int i = 0; i < 2; ++i)
+        acc[i] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(f.a[i], f.b, acc[i], 0, 0, SS, sa[i], SS, sb);
+      return;
+    }
 #pragma unroll
     for (int tt = 0; tt < 4; ++tt) {
       const int c = tt >> 1, d = 4 * c + 2 * (tt & 1);
@@ -1152,10 +898,10 @@ int launch_products(const Problem &pb, const DeviceTables &tab, const uint8_t *w
   g.w = tab.w_inner;
   const dim3 grid((unsigned)(tiles_m * tiles_n), (unsigned)pb.To, (unsigned)pb.batch);
   const bool mx = !pb.exact_dot && pb.rule != dev::RULE_FP32_AMAX && (pb.block == 32 || pb.block == 128);
-  // the 128 x 128 tile layout: E8M0 scales at blocks 32 and 128 (fp8 path, or
-  // the exact-dot path with each block's power of two folded into the codes)
+  // the 128 x 128 tile layout: E8M0 scales (the fp8 path at blocks 32 and 128,
+  // or the exact-dot path with each block's power of two folded into the codes)
   const bool aligned = pb.layout == FMM_LAYOUT_TILE128x128;
-  if (aligned && (pb.exact_dot || pb.block == 16)) {
+  if (aligned) {
     // one persistent workgroup per CU (its LDS ring and registers fill one)
     const int64_t items = tiles_m * tiles_n * pb.To * pb.batch;
     int dev = 0, ncu = 0;
@@ -1164,20 +910,20 @@ int launch_products(const Problem &pb, const DeviceTables &tab, const uint8_t *w
       ncu = 256;
     if (items > INT32_MAX) return hipErrorInvalidValue;
     const dim3 pgrid((unsigned)(items < ncu ? items : ncu));
-#define FMM_DQ8(BSV) \
-  hipLaunchKernelGGL((gemm_dq8_kernel<BSV>), pgrid, dim3(kDqThreads), 0, st, g, (int)tiles_m, (int)items)
+#define FMM_TILE128(BSV, EXACT) \
+  hipLaunchKernelGGL((gemm_tile128_kernel<BSV, EXACT>), pgrid, dim3(kTileThreads), 0, st, g, (int)tiles_m, (int)items)
     if (pb.block == 16)
-      FMM_DQ8(16);
+      FMM_TILE128(16, true);
+    else if (pb.block == 32 && pb.exact_dot)
+      FMM_TILE128(32, true);
     else if (pb.block == 32)
-      FMM_DQ8(32);
+      FMM_TILE128(32, false);
+    else if (pb.exact_dot)
+      FMM_TILE128(128, true);
     else
-      FMM_DQ8(128);
-#undef FMM_DQ8
-  } else if (aligned && pb.block == 32)
-    hipLaunchKernelGGL(gemm_mx_fast_kernel<32>, grid, dim3(kThreads), 0, st, g, (int)tiles_m);
-  else if (aligned)
-    hipLaunchKernelGGL(gemm_mx_fast_kernel<128>, grid, dim3(kThreads), 0, st, g, (int)tiles_m);
-  else if (mx)
+      FMM_TILE128(128, false);
+#undef FMM_TILE128
+  } else if (mx)
     hipLaunchKernelGGL(gemm_mx_kernel, grid, dim3(kThreads), 0, st, g);
   else
     hipLaunchKernelGGL(gemm_promote_kernel, grid, dim3(kThreads), 0, st, g, pb.scale_bytes);
