@@ -502,7 +502,7 @@ def main():
     elif a_view.code_layout == 2:
         prod_kernel = "gemm_tile128_kernel"
     else:
-        prod_kernel = "gemm_promote_kernel" if exact else "gemm_mx_kernel"
+        prod_kernel = "gemm_terms_kernel" if exact else "gemm_mx_kernel"
     traffic = None
     step_traffic = None
     if counters:

@@ -14,15 +14,16 @@ ROCM = os.environ.get("ROCM_PATH", "/opt/rocm")
 HIPCC = os.path.join(ROCM, "bin", "hipcc")
 
 SOURCES = ["realization.cpp", "optimize.cpp", "plan.cpp", "kernels_encode.hip", "kernels_gemm.hip",
-           "kernels_split.hip", "kernels_measure.hip", "kernels_cross.hip"]
+           "kernels_terms.hip", "kernels_split.hip", "kernels_measure.hip", "kernels_cross.hip"]
 
 COMMON = ["-O3", "-std=c++17", "-fPIC", "-ffp-contract=off", "-Wall",
           "-Wno-unused-function", "-Wno-unused-variable"]
 DEVICE = ["--offload-arch=gfx950", "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
           "-munsafe-fp-atomics"]
-# the 128 x 128 kernels keep the MFMA accumulators in VGPRs, beside the W-combine
-# quadrants they are added to; the 256 x 256 kernel keeps its 256 accumulators in AGPRs
-PER_FILE = {"kernels_gemm.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"]}
+# the 128 x 128 and per-term kernels keep the MFMA accumulators in VGPRs, beside the W-combine
+# quadrants or fragments they work on; the 256 x 256 kernel keeps its 256 accumulators in AGPRs
+PER_FILE = {"kernels_gemm.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"],
+            "kernels_terms.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"]}
 
 
 def _compile(src: str) -> str:

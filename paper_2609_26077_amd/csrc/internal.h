@@ -87,6 +87,7 @@ struct Problem {
   // set `shaped` and run at one level on the large-tile path)
   int gm, gk, gn;
   int shaped;
+  int ncu;                 // compute units of the plan's device
 };
 
 // The dense coefficient rows of a plan of another shape are padded with zeros
@@ -137,6 +138,12 @@ int launch_products(const Problem &pb, const DeviceTables &tab, const uint8_t *w
 // what remains of the W-combine after launch_products (nothing for fused depth-1 plans)
 int launch_combine(const Problem &pb, const DeviceTables &tab, const uint8_t *ws, const Workspace &wl,
                    float *C, void *stream);
+// the sub-products of a fused plan (128 x 128 tiled or row layout) with one
+// wave per inner term, on tiles of `edge` (32 or 64) rows and columns; and the
+// edge that suits the plan (0: the plan has 128 x 128 tiles enough)
+int terms_edge(const Problem &pb);
+int launch_products_terms(const Problem &pb, const DeviceTables &tab, const uint8_t *ws, const Workspace &wl,
+                          float *C, int edge, void *stream);
 int launch_products_split(const Problem &pb, const uint8_t *ws, const Workspace &wl, void *stream);
 int launch_combine_split(const Problem &pb, const DeviceTables &tab, const uint8_t *ws, const Workspace &wl,
                          float *C, void *stream);

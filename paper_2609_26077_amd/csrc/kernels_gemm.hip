@@ -21,13 +21,14 @@
 // products to the group's largest and keeps 13 bits below it (measured:
 // 1 + 2^-13 survives, 1 + 2^-14 returns 1; groups are summed at fp32 grade).
 //
-// Exact-dot paths (FMM_FLAG_EXACT_DOT, fp32 scales or block 16): the codes are
-// converted exactly to bf16 and fed to v_mfma_f32_32x32x16_bf16 (lane (r, h)
-// holds row r, elements [8h, 8h+8); 23 retained bits).  With E8M0 scales on
-// the tile layout (gemm_tile128_kernel) each code's conversion applies its block's
-// power of two; otherwise (gemm_promote_kernel) the codes convert at scale 1,
-// each block's products are summed in a temporary and scaled by sA * sB in
-// fp32 -- in both, the products of the dequantized operands accumulated in fp32.
+// Exact-dot path (FMM_FLAG_EXACT_DOT, or block 16) with E8M0 scales on the tile
+// layout (gemm_tile128_kernel): each code is converted exactly to bf16 with its
+// block's power of two and fed to v_mfma_f32_32x32x16_bf16 (lane (r, h)
+// holds row r, elements [8h, 8h+8); 23 retained bits), so the products of the
+// dequantized operands are accumulated in fp32.
+//
+// Products with few tiles, and the other exact-dot plans in the row layout,
+// run on gemm_terms_kernel (one wave per inner term).
 //
 // Output layout of the 32x32 instructions: lane l, register j holds
 // column l % 32, row 8 (j / 4) + 4 (l / 32) + j % 4.
@@ -47,18 +48,6 @@ typedef int v8i __attribute__((ext_vector_type(8)));
 typedef float v16f __attribute__((ext_vector_type(16)));
 typedef __bf16 v8bf __attribute__((ext_vector_type(8)));
 typedef __bf16 v2bf __attribute__((ext_vector_type(2)));
-
-// eight e4m3 codes (little-endian in two words) -> eight bf16, exactly
-__device__ __forceinline__ v8bf e4m3x8_to_bf16(uint2 w) {
-  const v2bf a = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8((int)w.x, 1.0f, false);
-  const v2bf b = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8((int)w.x, 1.0f, true);
-  const v2bf c = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8((int)w.y, 1.0f, false);
-  const v2bf d = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8((int)w.y, 1.0f, true);
-  v8bf r;
-  r[0] = a[0]; r[1] = a[1]; r[2] = b[0]; r[3] = b[1];
-  r[4] = c[0]; r[5] = c[1]; r[6] = d[0]; r[7] = d[1];
-  return r;
-}
 
 constexpr int BM = 128, BN = 128, BK = 128;
 constexpr int kThreads = 256;
@@ -653,146 +642,6 @@ __global__ __launch_bounds__(kTileThreads, 1) void gemm_tile128_kernel(GemmArgs 
 }
 
 // ---------------------------------------------------------------------------
-// Promotion path: fp32 block scales (or block 16)
-// ---------------------------------------------------------------------------
-
-constexpr int kMaxKbPerStep = BK / 16;   // block 16 -> 8 blocks per k-step
-
-__global__ __launch_bounds__(kThreads, 1) void gemm_promote_kernel(GemmArgs g, int scale_bytes) {
-  __shared__ uint4 lds_raw[2 * 2 * BM * BK / 16];
-  __shared__ float lsa[BM * kMaxKbPerStep];
-  __shared__ float lsb[BN * kMaxKbPerStep];
-  uint8_t *lds = reinterpret_cast<uint8_t *>(lds_raw);
-  const int t = threadIdx.x;
-  const int wave = t >> 6, lane = t & 63;
-  const int wm = wave >> 1, wn = wave & 1;
-  const int r32 = lane & 31, h = lane >> 5;
-  const int64_t tm = blockIdx.x / g.tiles_n, tn = blockIdx.x % g.tiles_n;
-  const int64_t ro = blockIdx.y, bt = blockIdx.z;
-  const int64_t pm0 = tm * BM, pn0 = tn * BN;
-  const int64_t rowa0 = pm0 + wm * 64, rowb0 = pn0 + wn * 64;
-  const int64_t nsteps = (g.kp + BK - 1) / BK;
-  const int64_t total = (int64_t)g.R * nsteps;
-  const int kb_step = BK / g.block > 0 ? BK / g.block : 1;  // blocks per k-step (block <= 128)
-  const int chunks_per_block = g.block / 16;
-
-  v16f acc[2][2], quad[4][2][2];
-#pragma unroll
-  for (int i = 0; i < 2; ++i)
-#pragma unroll
-    for (int j = 0; j < 2; ++j) {
-      acc[i][j] = (v16f){};
-#pragma unroll
-      for (int q = 0; q < 4; ++q) quad[q][i][j] = (v16f){};
-    }
-
-  Stage st;
-  load_stage(g, bt, ro * g.R, 0, pm0, pn0, st);
-  store_stage(lds, lds + BM * BK, st);
-
-  for (int64_t it = 0; it < total; ++it) {
-    const int ri = (int)(it / nsteps);
-    const int64_t ks = it % nsteps;
-    const int64_t r = ro * g.R + ri;
-    const int buf = (int)(it & 1);
-    const bool more = it + 1 < total;
-    // scales of this step into LDS (fp32 values)
-    for (int e = t; e < (BM + BN) * kb_step; e += kThreads) {
-      const bool isb = e >= BM * kb_step;
-      const int ee = isb ? e - BM * kb_step : e;
-      const int row = ee / kb_step, kbl = ee % kb_step;
-      const int64_t kb = ks * kb_step + kbl;
-      const int64_t p = (isb ? pn0 : pm0) + row;
-      const int64_t rows = isb ? g.np : g.mp;
-      float v = 0.f;
-      if (p < rows && kb < g.kblocks) {
-        const int64_t idx = ((bt * g.T + r) * rows + p) * g.kblocks + kb;
-        const uint8_t *base = isb ? g.sb : g.sa;
-        if (scale_bytes == 4)
-          v = reinterpret_cast<const float *>(base)[idx];
-        else
-          v = __uint_as_float((uint32_t)base[idx] << 23);   // 2^(e8m0 - 127)
-      }
-      (isb ? lsb : lsa)[row * kMaxKbPerStep + kbl] = v;
-    }
-    __syncthreads();
-    if (more) {
-      const int64_t rn = ro * g.R + (it + 1) / nsteps;
-      const int64_t kn = ((it + 1) % nsteps) * BK;
-      load_stage(g, bt, rn, kn, pm0, pn0, st);
-    }
-    const uint8_t *la = lds + buf * 2 * BM * BK;
-    const uint8_t *lb = la + BM * BK;
-    for (int kbl = 0; kbl < kb_step; ++kbl) {
-      v16f tmp[2][2];
-#pragma unroll
-      for (int i = 0; i < 2; ++i)
-#pragma unroll
-        for (int j = 0; j < 2; ++j) tmp[i][j] = (v16f){};
-      for (int cc = 0; cc < chunks_per_block; ++cc) {
-        const int c = kbl * chunks_per_block + cc;   // 16-byte chunk within the step
-        v8bf fa[2], fb[2];
-#pragma unroll
-        for (int i = 0; i < 2; ++i) {
-          const int rowa = wm * 64 + 32 * i + r32, rowb = wn * 64 + 32 * i + r32;
-          fa[i] = e4m3x8_to_bf16(*reinterpret_cast<const uint2 *>(la + swz(rowa, c) + 8 * h));
-          fb[i] = e4m3x8_to_bf16(*reinterpret_cast<const uint2 *>(lb + swz(rowb, c) + 8 * h));
-        }
-#pragma unroll
-        for (int i = 0; i < 2; ++i)
-#pragma unroll
-          for (int j = 0; j < 2; ++j)
-            tmp[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[i], fb[j], tmp[i][j], 0, 0, 0);
-      }
-      // promote: acc += sA[row] sB[col] tmp
-#pragma unroll
-      for (int i = 0; i < 2; ++i)
-#pragma unroll
-        for (int j = 0; j < 2; ++j) {
-          const float sbv = lsb[(wn * 64 + 32 * j + r32) * kMaxKbPerStep + kbl];
-#pragma unroll
-          for (int e = 0; e < 16; ++e) {
-            const int row = wm * 64 + 32 * i + 8 * (e >> 2) + 4 * h + (e & 3);
-            const float s = lsa[row * kMaxKbPerStep + kbl] * sbv;
-            acc[i][j][e] = __fmaf_rn(s, tmp[i][j][e], acc[i][j][e]);
-          }
-        }
-    }
-    if (ks == nsteps - 1) {
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const float wq = g.w[4 * ri + q];
-        if (wq != 0.0f) {
-#pragma unroll
-          for (int i = 0; i < 2; ++i)
-#pragma unroll
-            for (int j = 0; j < 2; ++j)
-#pragma unroll
-              for (int e = 0; e < 16; ++e) quad[q][i][j][e] = __fmaf_rn(wq, acc[i][j][e], quad[q][i][j][e]);
-        }
-      }
-#pragma unroll
-      for (int i = 0; i < 2; ++i)
-#pragma unroll
-        for (int j = 0; j < 2; ++j) acc[i][j] = (v16f){};
-    }
-    __syncthreads();   // everyone is done with this buffer and with lsa/lsb
-    if (more) {
-      uint8_t *na = lds + (buf ^ 1) * 2 * BM * BK;
-      store_stage(na, na + BM * BK, st);
-    }
-  }
-
-#pragma unroll
-  for (int q = 0; q < 4; ++q)
-#pragma unroll
-    for (int i = 0; i < 2; ++i)
-#pragma unroll
-      for (int j = 0; j < 2; ++j)
-        store_tile(g, bt, ro, q, rowa0 + 32 * i, rowb0 + 32 * j, quad[q][i][j]);
-}
-
-// ---------------------------------------------------------------------------
 // Outer combine (depth >= 2): C block (I, K) with I = 2 I_o + i, K = 2 K_o + k:
 //   C = sum_{r_o} w_outer[r_o][K_o 2^(l-1) + I_o] * Q[r_o][2k + i]
 // ---------------------------------------------------------------------------
@@ -883,6 +732,8 @@ int launch_products(const Problem &pb, const DeviceTables &tab, const uint8_t *w
                     const Workspace &wl, float *C, void *stream) {
   if (pb.batch == 0 || pb.M == 0 || pb.N == 0) return hipSuccess;
   if (pb.split) return launch_products_split(pb, ws, wl, stream);
+  const int edge = terms_edge(pb);
+  if (edge) return launch_products_terms(pb, tab, ws, wl, C, edge, stream);
   hipStream_t st = reinterpret_cast<hipStream_t>(stream);
   GemmArgs g;
   g.xa = ws + wl.a_codes;
@@ -897,19 +748,14 @@ int launch_products(const Problem &pb, const DeviceTables &tab, const uint8_t *w
   g.tiles_n = (int)tiles_n;
   g.w = tab.w_inner;
   const dim3 grid((unsigned)(tiles_m * tiles_n), (unsigned)pb.To, (unsigned)pb.batch);
-  const bool mx = !pb.exact_dot && pb.rule != dev::RULE_FP32_AMAX && (pb.block == 32 || pb.block == 128);
   // the 128 x 128 tile layout: E8M0 scales (the fp8 path at blocks 32 and 128,
   // or the exact-dot path with each block's power of two folded into the codes)
   const bool aligned = pb.layout == FMM_LAYOUT_TILE128x128;
   if (aligned) {
     // one persistent workgroup per CU (its LDS ring and registers fill one)
     const int64_t items = tiles_m * tiles_n * pb.To * pb.batch;
-    int dev = 0, ncu = 0;
-    if (hipGetDevice(&dev) != hipSuccess ||
-        hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || ncu <= 0)
-      ncu = 256;
     if (items > INT32_MAX) return hipErrorInvalidValue;
-    const dim3 pgrid((unsigned)(items < ncu ? items : ncu));
+    const dim3 pgrid((unsigned)(items < pb.ncu ? items : pb.ncu));
 #define FMM_TILE128(BSV, EXACT) \
   hipLaunchKernelGGL((gemm_tile128_kernel<BSV, EXACT>), pgrid, dim3(kTileThreads), 0, st, g, (int)tiles_m, (int)items)
     if (pb.block == 16)
@@ -923,10 +769,9 @@ int launch_products(const Problem &pb, const DeviceTables &tab, const uint8_t *w
     else
       FMM_TILE128(128, false);
 #undef FMM_TILE128
-  } else if (mx)
-    hipLaunchKernelGGL(gemm_mx_kernel, grid, dim3(kThreads), 0, st, g);
-  else
-    hipLaunchKernelGGL(gemm_promote_kernel, grid, dim3(kThreads), 0, st, g, pb.scale_bytes);
+  } else {
+    hipLaunchKernelGGL(gemm_mx_kernel, grid, dim3(kThreads), 0, st, g);   // (fp8, row layout)
+  }
   return hipGetLastError();
 }
 

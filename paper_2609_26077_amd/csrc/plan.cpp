@@ -126,6 +126,7 @@ int fmm_plan_create(const fmm_real *d, const fmm_plan_desc *desc, fmm_plan **out
   pb.scale_bytes = q.rule == FMM_RULE_FP32_AMAX ? 4 : 1;
   pb.exact_dot = (q.flags & FMM_FLAG_EXACT_DOT) ? 1 : 0;
   pb.b_rows = (q.flags & FMM_FLAG_B_BLOCK128) ? 128 : 1;
+  pb.ncu = 256;   // (replaced by the device's own count below)
   pb.b_bf16 = (q.flags & FMM_FLAG_B_BF16) ? 1 : 0;
   // E8M0 scales have a fused 128 x 128 kernel: at blocks 32 and 128 on either
   // path (the fp8 matrix cores, or the exact-dot flag's folded-scale form),
@@ -241,6 +242,8 @@ int fmm_plan_create(const fmm_real *d, const fmm_plan_desc *desc, fmm_plan **out
     return FMM_ERR_DEVICE;
   }
   p->device = dev;
+  int ncu = 0;
+  if (hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess && ncu > 0) pb.ncu = ncu;
   void *dt = nullptr;
   int e = hipMalloc(&dt, tot);
   if (e == hipSuccess) e = hipMemcpy(dt, host.data(), tot, hipMemcpyHostToDevice);
