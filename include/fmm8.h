@@ -110,11 +110,12 @@ enum {
   FMM_FLAG_B_BF16 = 4,
   /* Take the large-tile sub-product path (FMM_LAYOUT_TILE256x64) whenever
    * the shape allows it.  Without the flag, plans on the fp8 matrix cores
-   * take that path only where K / 2^l >= 1024: it writes every fp32 P_r to
-   * the workspace and reads it back, which costs more than it saves on short
-   * contractions (exact-dot plans take it whenever the shape allows).  No
-   * effect on the result's definition; shapes the path cannot take ignore
-   * the flag. */
+   * take that path only where K / 2^l >= 1024, and at depth 1 not where the
+   * product's 128 x 128 tiles fill the chip and K / 2 is at most about 2048: it
+   * writes every fp32 P_r to the workspace and reads it back, which costs more
+   * than it saves there (plans with fp32 scales take it whenever the shape
+   * allows).  No effect on the result's definition; shapes the path cannot
+   * take ignore the flag. */
   FMM_FLAG_LARGE_TILE = 8
 };
 
@@ -145,7 +146,7 @@ enum {
    * Used by plans whose sub-products run on 256-row tiles: depth 1 or 2,
    * M / 2^l and N / 2^l multiples of 256, K / 2^l a multiple of 64 (of 128
    * at block 128), and either fp32 scales (the exact-dot path) or E8M0
-   * scales with K / 2^l >= 1024 or FMM_FLAG_LARGE_TILE (the fp8 matrix cores
+   * scales with FMM_FLAG_LARGE_TILE or K / 2^l >= 1024 (see there) (the fp8 matrix cores
    * at blocks 32 and 128, the exact-dot path at block 16 or with
    * FMM_FLAG_EXACT_DOT); and every plan of a
    * realization of another shape (rows M / m and N / n, kdim K / k).  The B

@@ -2,6 +2,7 @@
 #include <hip/hip_runtime_api.h>
 
 #include <algorithm>
+#include <cmath>
 #include <cstring>
 #include <new>
 #include <string>
@@ -25,6 +26,28 @@ bool is_gfx950(int dev) {
   hipDeviceProp_t prop;
   if (hipGetDeviceProperties(&prop, dev) != hipSuccess) return false;
   return std::strncmp(prop.gcnArchName, "gfx950", 6) == 0;
+}
+
+// Whether the fused 128 x 128 kernel beats the large tiles and their W-combine
+// pass on a depth-1 product with E8M0 scales and k' >= 1024: it writes no P_r,
+// but a round of one tile per CU costs the same however many CUs it fills,
+// and its smaller tiles need twice the L2 bytes per flop, so it wins where the
+// tiles fill their rounds and k' is not large.  Times in us, fitted to
+// measurement (fused / large tiles + combine, T*, block 32; fp8, then
+// exact-dot): 4096x2048x4096 53 / 78 and 71 / 91; 8192x2048x8192 213 / 261 and
+// 290 / 329; 16 of 2048^3 206 / 262 and 287 / 331; 4096^3 89 / 99 and 132 /
+// 139; and the other way round 3072x2048x3072 48 / 46, 65 / 53; 6144x4096x6144
+// 243 / 201, 356 / 287; 4096x8192x4096 160 / 144, 253 / 238; 8192^3 634 /
+// 530, 987 / 854.
+bool fused_beats_large_tiles(int64_t batch, int64_t R, int64_t mp, int64_t kp, int64_t np, bool exact) {
+  constexpr double kCUs = 256;
+  const double outputs = (double)batch * mp * np, k = (double)kp;
+  const double fused_rounds = std::ceil(outputs / (128 * 128) / kCUs);
+  const double fused = R * fused_rounds * (exact ? 1.5 + 1.09 * k / 128 : 2.1 + 0.66 * k / 128);
+  const double large_rounds = std::ceil(R * outputs / (256 * 256) / kCUs);   // (exact-dot: two 256 x 128 tiles per CU)
+  const double large = large_rounds * (exact ? 16 + 22.5 * k / 1024 : 9 + 12.5 * k / 1024) +
+                       4 * (R + 4) * outputs / 6.4e6;                        // the combine's bytes at 6.4 TB/s
+  return fused < large;
 }
 
 }  // namespace
@@ -100,9 +123,9 @@ int fmm_plan_create(const fmm_real *d, const fmm_plan_desc *desc, fmm_plan **out
   // bytes per output of each term) and reads it back, 8 / k' bytes per flop
   // against the fused path's none: plans with a fused kernel take it by
   // default where that round trip costs less than the fused path's smaller
-  // tiles, k' >= 1024 (measured on both forms: the large tiles win at 1024
-  // and above, lose at 512 and below); fp32 scales whenever the shape allows
-  // (their fused promote kernel is slower at every measured k').
+  // tiles: k' >= 1024 (they lose at 512 and below at every size measured), and
+  // at depth 1 only where fused_beats_large_tiles does not hold; fp32 scales
+  // whenever the shape allows.
   // Plans of other shapes take it always (their W-combine fans each P_r out
   // to up to m n blocks of C), K = 0 included (C is then zero).
   const int64_t mp = q.M / gm, kp = q.K / gk, np = q.N / gn;
@@ -133,8 +156,11 @@ int fmm_plan_create(const fmm_real *d, const fmm_plan_desc *desc, fmm_plan **out
   // at block 16 the folded-scale form (block 16 always runs exact-dot); fp32
   // scales only the large-tile exact-dot kernels
   const bool fused_exists = pb.scale_bytes == 1 && (q.block == 16 || q.block == 32 || q.block == 128);
-  pb.split = shaped || (split_shape &&
-             (!fused_exists || pb.kp >= fmm::kSplitMinK || (q.flags & FMM_FLAG_LARGE_TILE)));
+  const bool exact = pb.exact_dot || q.block == 16;
+  const bool fused_fills = q.depth == 1 && pb.kp % 128 == 0 &&
+                           fused_beats_large_tiles(q.batch, T, mp, kp, np, exact);
+  pb.split = shaped || (split_shape && (!fused_exists || (q.flags & FMM_FLAG_LARGE_TILE) ||
+                                        (pb.kp >= fmm::kSplitMinK && !fused_fills)));
   // fused 128 x 128 path: E8M0 scales at blocks 32 and 128 (the fp8 matrix
   // cores, or the exact-dot flag's folded-scale bf16 form) and block 16 (the
   // folded-scale form), whole 128-row tiles and 128-byte K steps

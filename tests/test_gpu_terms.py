@@ -61,3 +61,29 @@ def test_mx_rows_full_rounds(bs):
     fp8 plan takes gemm_mx_kernel, on ragged edges of both sides."""
     check_case("strassen", "gaussian", 1, 2 * (15 * 128 + 5), 2 * (bs + 128), 2 * (13 * 128 + 7), 1, bs, 1, seed=35, cfg=2,
                layout=ROWS)
+
+
+@pytest.mark.parametrize("case", [
+    (1, 4096, 2048, 4096, 2),     # one full round of 128 x 128 tiles, k' = 1024: fused
+    (1, 4096, 4096, 4096, 2),     # k' = 2048: fused
+    (3, 2048, 2048, 2048, 2),     # 192 tiles: fused
+    (1, 3072, 3072, 3072, 1),     # 144 tiles: large tiles
+    (1, 4096, 8192, 4096, 1),     # k' = 4096: large tiles
+])
+@pytest.mark.parametrize("exact", [False, True])
+def test_fused_or_large_tiles(case, exact):
+    """Depth 1 from k' = 1024 on: which path a plan takes, and that C is the
+    large tiles' bit for bit (both sum a term's products in the same order and
+    add the terms in ascending order by one fused multiply-add)."""
+    import torch
+    from paper_2609_26077_amd import FMM_FLAG_LARGE_TILE, fmm_operand_views
+    from paper_2609_26077_amd.runner import FMM
+    b, M, K, N, layout = case
+    g = torch.Generator(device="cuda").manual_seed(7)
+    A = torch.randn((b, M, K), generator=g, device="cuda")
+    B = torch.randn((b, K, N), generator=g, device="cuda")
+    f = FMM("tstar", b, M, K, N, 1, 32, "pow2_ceil", exact_dot=exact)
+    assert fmm_operand_views(f.plan, f.ws)[0].code_layout == layout
+    large = FMM("tstar", b, M, K, N, 1, 32, "pow2_ceil", exact_dot=exact, flags=FMM_FLAG_LARGE_TILE)
+    assert fmm_operand_views(large.plan, large.ws)[0].code_layout == 1
+    assert torch.equal(f.matmul(A, B), large.matmul(A, B))
