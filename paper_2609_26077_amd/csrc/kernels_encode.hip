@@ -293,32 +293,30 @@ constexpr bool narrow_b(int side, int depth, int bs, int mode) {
   return side == 1 && depth == 2 && bs <= 32 && mode == 0;
 }
 
-template <int SIDE, int DEPTH, int BS, bool F32, int MODE, int CAP = 0, bool N1 = false>
-__global__ __launch_bounds__((Tile<DEPTH, 16, SIDE, narrow_b(SIDE, DEPTH, BS, MODE) || N1>::threads)) void encode16_kernel(
-    const float *__restrict__ src, Problem pb, SideTab cf, uint8_t *__restrict__ codes, uint8_t *__restrict__ scales,
-    int64_t tiles_l, void *__restrict__ aux) {
+// The work of one workgroup of NT threads: tile bx of nbx (of product bt) of one side.
+template <int SIDE, int DEPTH, int BS, bool F32, int MODE, int CAP, bool N1, int NT>
+__device__ __forceinline__ void encode16_tile(float *lds, const float *__restrict__ src, const Problem &pb, const SideTab &cf,
+                                              uint8_t *__restrict__ codes, uint8_t *__restrict__ scales, int64_t tiles_l,
+                                              void *__restrict__ aux, unsigned bx, unsigned nbx, int64_t bt) {
   static_assert(MODE == 0 || MODE == 3 || (SIDE == 1 && DEPTH == 1), "deployment granularity: B side, depth 1");
   static_assert(CAP == 0 || (MODE == 0 && (DEPTH == 1 || CAP == 16)), "other shapes: the plain encoder");
   constexpr bool GEN = CAP != 0;
   uint32_t *amax = reinterpret_cast<uint32_t *>(aux);
   using TT = Tile<DEPTH, 16, SIDE, narrow_b(SIDE, DEPTH, BS, MODE) || N1, CAP>;
-  constexpr int TR = TT::TR, NB = TT::nblk, NT = TT::threads, TL = TT::TL, STR = TT::stride;
+  constexpr int TR = TT::TR, NB = TT::nblk, TL = TT::TL, STR = TT::stride;
   constexpr int RPW = 64 * 16 / TL;         // rows per wave: 8, or 16 in the narrow tile
   constexpr int WPT = TR / RPW;             // waves per term (1 (A), 4 (B) or 2 (narrow B) at depth 1, 1 at depth 2)
   constexpr int TSTEP = NT / 64 / WPT;      // terms a workgroup works on at once
-  __shared__ float4 lds4[TT::lds_floats / 4];
-  float *lds = reinterpret_cast<float *>(lds4);
 
   const int t = threadIdx.x;
-  const int64_t bt = blockIdx.y;
   // depth-1 B side: the column tile varies fastest over the workgroups, so
   // neighbouring workgroups read adjacent 128-byte pieces of the same rows of
   // B at about the same time (the narrower tiles of depths 2 and 3 instead
   // rely on the neighbouring columns' tile running on the same XCD)
-  const int64_t tiles_r = gridDim.x / tiles_l;
+  const int64_t tiles_r = nbx / tiles_l;
   constexpr bool qfast = SIDE == 1 && DEPTH == 1 && MODE != 3;
-  const int64_t row0 = (qfast ? blockIdx.x % tiles_r : blockIdx.x / tiles_l) * TR;
-  const int64_t l0 = (qfast ? blockIdx.x / tiles_r : blockIdx.x % tiles_l) * TL;
+  const int64_t row0 = (qfast ? bx % tiles_r : bx / tiles_l) * TR;
+  const int64_t l0 = (qfast ? bx / tiles_r : bx % tiles_l) * TL;
   const int64_t rows = SIDE == 0 ? pb.mp : pb.np;
   stage_tile<SIDE, NB, TR, NT, TL, GEN>(lds, src, pb, bt, row0, l0, t);
   __syncthreads();
@@ -436,7 +434,7 @@ __global__ __launch_bounds__((Tile<DEPTH, 16, SIDE, narrow_b(SIDE, DEPTH, BS, MO
       }
       if (lane == 0) {
         double *pp = reinterpret_cast<double *>(aux) +
-                     ((((int64_t)bt * gridDim.x + blockIdx.x) * (NT / 64) + wave) * T + r) * 2;
+                     ((((int64_t)bt * nbx + bx) * (NT / 64) + wave) * T + r) * 2;
         pp[0] = e2;
         pp[1] = x2;
       }
@@ -504,6 +502,54 @@ __global__ __launch_bounds__((Tile<DEPTH, 16, SIDE, narrow_b(SIDE, DEPTH, BS, MO
       *reinterpret_cast<uint4 *>(codes + plane * code_plane + o.code) = make_uint4(w[0], w[1], w[2], w[3]);
     if (o.leader) store_scale(pb, scales, plane * scale_plane + o.scale, stored);
   }
+}
+
+template <int SIDE, int DEPTH, int BS, bool F32, int MODE, int CAP = 0, bool N1 = false>
+__global__ __launch_bounds__((Tile<DEPTH, 16, SIDE, narrow_b(SIDE, DEPTH, BS, MODE) || N1>::threads)) void encode16_kernel(
+    const float *__restrict__ src, Problem pb, SideTab cf, uint8_t *__restrict__ codes, uint8_t *__restrict__ scales,
+    int64_t tiles_l, void *__restrict__ aux) {
+  using TT = Tile<DEPTH, 16, SIDE, narrow_b(SIDE, DEPTH, BS, MODE) || N1, CAP>;
+  __shared__ float4 lds4[TT::lds_floats / 4];
+  encode16_tile<SIDE, DEPTH, BS, F32, MODE, CAP, N1, TT::threads>(reinterpret_cast<float *>(lds4), src, pb, cf, codes,
+                                                                  scales, tiles_l, aux, blockIdx.x, gridDim.x, blockIdx.y);
+}
+
+// Both sides of a <2,2,2> plan in one launch: workgroups 0 .. tiles[0] - 1 of a
+// product encode A, the rest B.  A small encode is two launches of about 5 us
+// that read a few megabytes each; in one launch the sides run side by side
+// (us, separate / one launch: 256^3 11.8 / 8.0, 1024^3 11.9 / 7.8, 100 of
+// 256^3 22.8 / 20.7, 4096^3 45.9 / 43.1; depth 2 1024^3 19.1 / 10.6, 4096^3
+// 71.5 / 62.5, 8192^3 286 / 274).  Both sides then have one workgroup size:
+// at depth 1 256 threads (A's four waves each take every fourth term; B on
+// the narrow tile) at blocks 16 and 32, 512 at block 128; at depth 2 1024, as
+// each has by itself.  Alternating the sides' workgroups: up to 9% slower.
+struct PairArgs {
+  const float *src[2];
+  SideTab cf[2];
+  uint8_t *codes[2], *scales[2];
+  int64_t tiles_l[2];
+  unsigned tiles[2];           // workgroups per product and side
+};
+
+template <int DEPTH, int BS>
+constexpr bool pair_n1() { return DEPTH == 1 && BS <= 32; }
+template <int DEPTH, int BS>
+constexpr int pair_threads() { return DEPTH == 2 ? 1024 : pair_n1<DEPTH, BS>() ? kB1NThreads : kB1Threads; }
+
+template <int DEPTH, int BS, bool F32>
+__global__ __launch_bounds__((pair_threads<DEPTH, BS>())) void encode_pair_kernel(Problem pb, PairArgs g) {
+  constexpr bool N1 = pair_n1<DEPTH, BS>();
+  constexpr int NT = pair_threads<DEPTH, BS>();
+  using TA = Tile<DEPTH, 16, 0>;
+  using TB = Tile<DEPTH, 16, 1, narrow_b(1, DEPTH, BS, 0) || N1>;
+  __shared__ float4 lds4[(TA::lds_floats > TB::lds_floats ? TA::lds_floats : TB::lds_floats) / 4];
+  float *lds = reinterpret_cast<float *>(lds4);
+  if (blockIdx.x < g.tiles[0])
+    encode16_tile<0, DEPTH, BS, F32, 0, 0, false, NT>(lds, g.src[0], pb, g.cf[0], g.codes[0], g.scales[0], g.tiles_l[0],
+                                                      nullptr, blockIdx.x, g.tiles[0], blockIdx.y);
+  else
+    encode16_tile<1, DEPTH, BS, F32, 0, 0, N1, NT>(lds, g.src[1], pb, g.cf[1], g.codes[1], g.scales[1], g.tiles_l[1],
+                                                   nullptr, blockIdx.x - g.tiles[0], g.tiles[1], blockIdx.y);
 }
 
 // ---------------------------------------------------------------------------
@@ -780,8 +826,7 @@ hipError_t launch_side(const Problem &pb, const float *src, const SideTab &cf,
     return launch_narrow4<SIDE, true>(pb, src, cf, codes, scales, st);
   }
   switch (pb.depth) {
-    case 1: return launch_wide<SIDE, 1>(pb, src, cf, codes, scales, st);
-    case 2: return launch_wide<SIDE, 2>(pb, src, cf, codes, scales, st);
+    case 1: return launch_wide<SIDE, 1>(pb, src, cf, codes, scales, st);   // (depth 2: launch_pair)
     case 3: return launch_narrow4<SIDE>(pb, src, cf, codes, scales, st);
   }
   return hipErrorInvalidValue;
@@ -907,10 +952,59 @@ int launch_encode_noise(const Problem &pb, const DeviceTables &tab, const float 
 }
 
 
+namespace {
+
+template <int DEPTH, int BS, bool F32>
+hipError_t launch_pair(const Problem &pb, PairArgs &g, hipStream_t st) {
+  using TA = Tile<DEPTH, 16, 0>;
+  using TB = Tile<DEPTH, 16, 1, narrow_b(1, DEPTH, BS, 0) || pair_n1<DEPTH, BS>()>;
+  auto tiles = [](int64_t n, int64_t t) { return (n + t - 1) / t; };
+  g.tiles_l[0] = tiles(pb.kp, TA::TL);
+  g.tiles_l[1] = tiles(pb.kp, TB::TL);
+  g.tiles[0] = (unsigned)(g.tiles_l[0] * tiles(pb.mp, TA::TR));
+  g.tiles[1] = (unsigned)(g.tiles_l[1] * tiles(pb.np, TB::TR));
+  const dim3 grid(g.tiles[0] + g.tiles[1], (unsigned)pb.batch);
+  hipLaunchKernelGGL((encode_pair_kernel<DEPTH, BS, F32>), grid, dim3(pair_threads<DEPTH, BS>()), 0, st, pb, g);
+  return hipGetLastError();
+}
+
+template <int DEPTH>
+hipError_t launch_pair_any(const Problem &pb, PairArgs &g, hipStream_t st) {
+  const bool f32 = pb.rule == dev::RULE_FP32_AMAX;
+  switch (pb.block) {
+    case 16: return f32 ? launch_pair<DEPTH, 16, true>(pb, g, st) : launch_pair<DEPTH, 16, false>(pb, g, st);
+    case 32: return f32 ? launch_pair<DEPTH, 32, true>(pb, g, st) : launch_pair<DEPTH, 32, false>(pb, g, st);
+    case 128: return f32 ? launch_pair<DEPTH, 128, true>(pb, g, st) : launch_pair<DEPTH, 128, false>(pb, g, st);
+  }
+  return hipErrorInvalidValue;
+}
+
+// One launch for both sides: always at depth 2; at depth 1 while the operands
+// are small enough that the launch saved outweighs A's best workgroup (two
+// waves; us, separate / one launch, block 32: 134 MB 45.9 / 43.1, 157 MB 52.1 /
+// 48.1, 302 MB 87.9 / 91.9, 537 MB 143 / 154; block 128: 33 MB 20.5 / 19.0,
+// 134 MB 59.4 / 61.6).
+bool one_launch(const Problem &pb) {
+  if (pb.shaped || pb.b_rows > 1 || pb.b_bf16 || pb.depth > 2) return false;
+  if (pb.depth == 2) return true;
+  const int64_t bytes = 4 * pb.batch * (pb.M * pb.K + pb.K * pb.N);
+  return bytes <= (pb.block == 128 ? int64_t(64) << 20 : int64_t(192) << 20);
+}
+
+}  // namespace
+
 int launch_encode(const Problem &pb, const DeviceTables &tab, const float *A, const float *B,
                   uint8_t *ws, const Workspace &wl, void *stream) {
   if (pb.batch == 0 || pb.M == 0 || pb.N == 0 || pb.K == 0) return hipSuccess;
   hipStream_t st = reinterpret_cast<hipStream_t>(stream);
+  if (one_launch(pb)) {
+    PairArgs g;
+    g.src[0] = A; g.src[1] = B;
+    g.cf[0] = a_tab(tab); g.cf[1] = b_tab(tab);
+    g.codes[0] = ws + wl.a_codes; g.codes[1] = ws + wl.b_codes;
+    g.scales[0] = ws + wl.a_scales; g.scales[1] = ws + wl.b_scales;
+    return pb.depth == 1 ? launch_pair_any<1>(pb, g, st) : launch_pair_any<2>(pb, g, st);
+  }
   hipError_t e = launch_side<0>(pb, A, a_tab(tab), ws + wl.a_codes, ws + wl.a_scales, st);
   if (e != hipSuccess) return e;
   if (pb.b_rows > 1 || pb.b_bf16)

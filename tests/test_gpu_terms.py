@@ -87,3 +87,37 @@ def test_fused_or_large_tiles(case, exact):
     large = FMM("tstar", b, M, K, N, 1, 32, "pow2_ceil", exact_dot=exact, flags=FMM_FLAG_LARGE_TILE)
     assert fmm_operand_views(large.plan, large.ws)[0].code_layout == 1
     assert torch.equal(f.matmul(A, B), large.matmul(A, B))
+
+
+@pytest.mark.parametrize("case", [
+    # (depth, bs, rule, M, K, N): one launch for both sides; uneven numbers of
+    # workgroups on the two sides, tiles that end partway in rows and positions
+    (1, 16, 0, 34, 160, 2), (1, 32, 1, 2, 192, 74), (1, 128, 2, 18, 768, 66), (1, 128, 0, 258, 256, 2),
+    (2, 16, 1, 36, 192, 4), (2, 32, 0, 4, 384, 68), (2, 128, 1, 40, 512, 36),
+])
+def test_encode_one_launch(case):
+    depth, bs, rule, M, K, N = case
+    check_case("winograd", "gaussian", 2, M, K, N, depth, bs, rule, seed=36, cfg=2, exact=True)
+
+
+def test_encode_two_launches():
+    """192 MiB of operands and more go to one launch per side: the same codes
+    and scales as two products of half the rows of A each (a row's codes depend
+    on that row alone; half the operands of A, one launch)."""
+    import torch
+    from paper_2609_26077_amd.runner import FMM
+    g = torch.Generator(device="cuda").manual_seed(8)
+    A = torch.randn((1, 12288, 4096), generator=g, device="cuda")
+    B = torch.randn((1, 4096, 512), generator=g, device="cuda")
+    whole = FMM("tstar", 1, 12288, 4096, 512, 1, 32, "pow2_ceil")
+    whole.encode(A, B)
+    codes, scales, bcodes, bscales = whole.operands()
+    h = 6144 // 2
+    for i in range(2):
+        # rows h i .. of both row blocks of A's grid
+        Ai = torch.cat([A[:, h * i:h * (i + 1)], A[:, 6144 + h * i:6144 + h * (i + 1)]], 1).contiguous()
+        half = FMM("tstar", 1, 6144, 4096, 512, 1, 32, "pow2_ceil")
+        half.encode(Ai, B)
+        c, s, bc, bs = half.operands()
+        assert torch.equal(c, codes[:, :, h * i:h * (i + 1)]) and torch.equal(s, scales[:, :, h * i:h * (i + 1)])
+        assert torch.equal(bc, bcodes) and torch.equal(bs, bscales)
