@@ -93,7 +93,7 @@ enum {
    * every scale the rules produce), with fp32 scales each block's partial
    * sum of codes is scaled and accumulated in fp32.  Half the peak rate of
    * the default path.  FP32_AMAX scales and block 16 always take this path;
-   * tile-aligned plans (FMM_LAYOUT_TILE256x64) on it run on 256 x 128 tiles
+   * tile-aligned plans with FP32_AMAX scales run on FMM_LAYOUT_TILE256x64
    * whatever K. */
   FMM_FLAG_EXACT_DOT = 1,
   /* Weight-side deployment granularity (Appendix E, weight-scale

@@ -16,8 +16,8 @@
 //      third: 8192^3 sub-products 0.47 -> 0.40 ms.
 //      Exact-dot plans take gemm_dq256x128_kernel (E8M0 scales: each block's
 //      power of two folded into the codes' conversion to bf16) or
-//      gemm_exact256x128_kernel (fp32 scales: per-block partial sums promoted
-//      in fp32) instead, on the same tiles and layouts.
+//      gemm_exact128x128_kernel (fp32 scales: per-block partial sums promoted
+//      in fp32) instead, on the same layouts.
 //   2. combine1_kernel: C block (i, k) = sum_r w[r][2k + i] P_r, ascending r,
 //      one fused multiply-add per nonzero weight (the order of the fused
 //      W-combine of the 128 x 128 path); combine2_kernel the same over the
@@ -433,13 +433,19 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_dq256x128_kernel(SplitArgs g
 // VALU operations against `block` multiply-adds on the matrix cores, so at
 // blocks 16 and 32 the promotes, not the matrix cores, bound the kernel.
 //
-// One workgroup of eight waves per (batch, term, 256 x 128 tile), each wave a
-// 64 x 64 quarter-column (2 x 2 tiles of v_mfma_f32_32x32x16_bf16), one
-// workgroup per CU.  The codes arrive through a 64-byte-step LDS ring like the
-// fp8 kernel's (four slots here, two steps ahead); each slot also holds the
-// step's scales: NB = max(1, 64 / block) K blocks of the 256 A rows and
-// max(2, NB) of the 128 B rows (block 128: the step's one block, repeated),
-// fp32 in row order.
+// One workgroup of four waves per (batch, term, 128 x 128 tile), each wave a
+// 64 x 64 quarter (2 x 2 tiles of v_mfma_f32_32x32x16_bf16), two workgroups per
+// CU.  The two waves that share a SIMD belong to different workgroups, so one's
+// promotes and conversions (VALU) run beside the other's matrix instructions;
+// eight waves of one workgroup on a 256 x 128 tile kept in step by its
+// barrier and paid for both in turn (8192^3 block 128 1041 -> 1018 us, block
+// 32 1463 -> 1383, block 16 2104 -> 2036; 4096^3 block 128 150 -> 132; 1024
+// products of 512^3 block 32 715 -> 626; 2048x4096x1024 block 16 75 -> 60, the
+// smaller tiles filling the chip better; C bit-identical).  The codes
+// arrive through a 64-byte-step LDS ring like the fp8 kernel's (four slots, two
+// steps ahead); each slot also holds the step's scales: max(2, 64 / block) K
+// blocks of the 128 rows of each side (block 128: the step's one block,
+// repeated), fp32 in row order.
 //
 // Each instruction's 16 contracted positions lie in one block, the same
 // positions on both operands, so every partial sum is over exactly one block.
@@ -449,17 +455,18 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_dq256x128_kernel(SplitArgs g
 // 32-byte group c.  Block 16: the instruction of block b takes bytes
 // 16 b + 8 h + 0..7 (an 8-byte read).
 namespace ex {
-constexpr int kThreadsX = 512;
+constexpr int kThreadsX = 256;
 constexpr int kSlotsX = 4;                       // two in flight, the current one, the previous one
+constexpr int TX = 128;                          // tile rows of A_r and of B_r: half an image each
+constexpr int kCode = TX * SK;                   // 8 KB of codes per side and step
 template <int BS>
 struct Geo {
-  static constexpr int SB = 4;                            // fp32 scale bytes
   static constexpr int NB = BS >= 64 ? 1 : 64 / BS;       // K blocks per step
-  static constexpr int NBB = NB < 2 ? 2 : NB;             // B scale blocks held per slot
-  static constexpr int kScaleA = NB * TM * SB;
-  static constexpr int kScaleB = NBB * TN * SB;
-  static constexpr int kSlot = kCodeA + kCodeB + kScaleA + kScaleB;
-  static_assert(kSlotsX * kSlot <= 160 * 1024, "one workgroup per CU");
+  static constexpr int NBB = NB < 2 ? 2 : NB;             // scale blocks held per side and slot
+  static constexpr int kBlock = TX * 4;                   // bytes of one block's scales
+  static constexpr int kScale = NBB * kBlock;
+  static constexpr int kSlot = 2 * kCode + 2 * kScale;
+  static_assert(2 * kSlotsX * kSlot <= 160 * 1024, "two workgroups per CU");
 };
 }  // namespace ex
 
@@ -478,9 +485,8 @@ __device__ __forceinline__ v8bfx codes8_to_bf16(uint32_t lo, uint32_t hi) {
 }
 
 template <int BS>
-__global__ __launch_bounds__(ex::kThreadsX, 1) void gemm_exact256x128_kernel(SplitArgs g) {
+__global__ __launch_bounds__(ex::kThreadsX, 2) void gemm_exact128x128_kernel(SplitArgs g) {
   using G = ex::Geo<BS>;
-  constexpr int SB = G::SB;
   constexpr int NB = G::NB;
   __shared__ uint4 lds_raw[ex::kSlotsX * G::kSlot / 16];
   const uint8_t *lds = reinterpret_cast<const uint8_t *>(lds_raw);
@@ -492,46 +498,35 @@ __global__ __launch_bounds__(ex::kThreadsX, 1) void gemm_exact256x128_kernel(Spl
   const int64_t nitems = (int64_t)gridDim.x;
   int64_t bt, r;
   int tm, tn;
-  work_of(blockIdx.x, nitems, g.T, g.tiles_m, g.tiles_n, bt, r, tm, tn);
-  const int64_t pm0 = (int64_t)tm * TM, pn0 = (int64_t)tn * TN;
-  const int hb = tn & 1;
+  work_of(blockIdx.x, nitems, g.T, 2 * g.tiles_m, g.tiles_n, bt, r, tm, tn);
+  const int64_t pm0 = (int64_t)tm * ex::TX, pn0 = (int64_t)tn * ex::TX;
   const int nk = (int)(g.kp / SK);
-  const uint8_t *xa = g.xa + ((bt * g.T + r) * g.tiles_m + tm) * (int64_t)nk * kImage;
-  const uint8_t *xb = g.xb + ((bt * g.T + r) * (g.tiles_n / 2) + (tn >> 1)) * (int64_t)nk * kImage + hb * kCodeB;
+  const uint8_t *xa = g.xa + ((bt * g.T + r) * g.tiles_m + (tm >> 1)) * (int64_t)nk * kImage + (tm & 1) * ex::kCode;
+  const uint8_t *xb = g.xb + ((bt * g.T + r) * (g.tiles_n / 2) + (tn >> 1)) * (int64_t)nk * kImage + (tn & 1) * ex::kCode;
   const uint32_t code_off = 16u * (uint32_t)lane;
-  // the three 1 KB code regions wave w moves each step: 3 w .. 3 w + 2
-  const uint8_t *csrc[3];
-  uint32_t cdst[3];
-#pragma unroll
-  for (int j = 0; j < 3; ++j) {
-    const int region = wave * 3 + j;
-    csrc[j] = region < 16 ? xa + region * 1024 : xb + (region - 16) * 1024;
-    cdst[j] = (uint32_t)(region < 16 ? region * 1024 : kCodeA + (region - 16) * 1024);
-  }
-  // one scale transfer per wave and step (16 bytes a lane):
-  //   waves 0..3: the 256 A rows of K block NB step + (wave mod NB) (block
-  //               128: of block step / 2; the extra waves repeat a transfer)
-  //   waves 4..7: the 128 B rows of K blocks NB step + 2 p + h into lane half
-  //               h, p = (wave - 4) mod (NB / 2) (blocks 32 and 128: p = 0;
-  //               block 128: both halves take block step / 2)
-  const bool s_is_a = wave < 4;
-  const int sblk = s_is_a ? wave % NB : 2 * ((wave - 4) % (G::NBB / 2));
-  const int64_t srows = s_is_a ? g.mp : g.np;
-  const uint8_t *sbase = (s_is_a ? g.sat + (bt * g.T + r) * g.kblocks * g.mp * SB + pm0 * SB
-                                 : g.sbt + (bt * g.T + r) * g.kblocks * g.np * SB + pn0 * SB);
-  const int64_t splane = srows * SB;                   // bytes per K block
-  const uint32_t s_off = 16u * (uint32_t)(s_is_a ? lane : r32);
-  const uint32_t sdst = (uint32_t)(kCodeA + kCodeB + (s_is_a ? sblk * TM * SB : G::kScaleA + sblk * TN * SB));
+  // the four 1 KB code regions wave w moves each step: 4 (w mod 2) .. + 3 of A
+  // (waves 0, 1) or B (waves 2, 3); and one transfer of scales, two K blocks of
+  // the same side's 128 rows, one per lane half: blocks 2 p, 2 p + 1 of the step,
+  // p = (w mod 2) mod (NB / 2) (block 32: p = 0; block 128: both halves take
+  // the step's one block)
+  const bool is_a = wave < 2;
+  const uint8_t *csrc = (is_a ? xa : xb) + (wave & 1) * 4096;
+  const uint32_t cdst = (uint32_t)((is_a ? 0 : ex::kCode) + (wave & 1) * 4096);
+  const int sblk = 2 * ((wave & 1) % (G::NBB / 2));
+  const int64_t srows = is_a ? g.mp : g.np;
+  const uint8_t *sbase = is_a ? g.sat + ((bt * g.T + r) * g.kblocks * g.mp + pm0) * 4
+                              : g.sbt + ((bt * g.T + r) * g.kblocks * g.np + pn0) * 4;
+  const int64_t splane = srows * 4;                    // bytes per K block
+  const uint32_t s_off = 16u * (uint32_t)r32 + (BS < 64 ? (uint32_t)(h * splane) : 0u);
+  const uint32_t sdst = (uint32_t)(2 * ex::kCode + (is_a ? 0 : G::kScale) + sblk * G::kBlock);
 
   auto issue = [&](int step) {
     const uint32_t m0 = lds_base + (uint32_t)(step % ex::kSlotsX) * G::kSlot;
     const int64_t src = (int64_t)step * kImage;
 #pragma unroll
-    for (int j = 0; j < 3; ++j) dma::copy16(code_off, csrc[j] + src, m0 + cdst[j]);
+    for (int j = 0; j < 4; ++j) dma::copy16(code_off, csrc + src + j * 1024, m0 + cdst + j * 1024);
     const int64_t kb = BS >= 64 ? step / 2 : (int64_t)NB * step + sblk;
-    // B lanes of half h read the next block (blocks 16, 32)
-    const uint32_t hoff = (!s_is_a && BS < 64) ? (uint32_t)(h * splane) : 0u;
-    dma::copy16(s_off + hoff, sbase + kb * splane, m0 + sdst);
+    dma::copy16(s_off, sbase + kb * splane, m0 + sdst);
   };
 
   v16f acc[2][2], part[2][2];
@@ -548,8 +543,8 @@ __global__ __launch_bounds__(ex::kThreadsX, 1) void gemm_exact256x128_kernel(Spl
   // in LDS then: the ring has four slots and refills the one of step s - 2
   // during step s, so the previous step's slot stays intact.
   auto promote = [&](const uint8_t *slot, int blk) {
-    const uint8_t *sa = slot + kCodeA + kCodeB + blk * TM * SB;
-    const uint8_t *sb = slot + kCodeA + kCodeB + G::kScaleA + blk * TN * SB;
+    const uint8_t *sa = slot + 2 * ex::kCode + blk * G::kBlock;
+    const uint8_t *sb = sa + G::kScale;
     // sB of the lane's column in column tile j
     float sbv[2];
 #pragma unroll
@@ -583,7 +578,7 @@ __global__ __launch_bounds__(ex::kThreadsX, 1) void gemm_exact256x128_kernel(Spl
   };
   auto mfma_step = [&](const uint8_t *la, const uint8_t *prev, auto FRESH) {
     constexpr bool fresh = decltype(FRESH)::value;
-    const uint8_t *lb = la + kCodeA;
+    const uint8_t *lb = la + ex::kCode;
     if (BS == 16) {
 #pragma unroll
       for (int blk = 0; blk < 4; ++blk) {
@@ -637,7 +632,7 @@ __global__ __launch_bounds__(ex::kThreadsX, 1) void gemm_exact256x128_kernel(Spl
   // slot of step s - 2, multiply step s.
   auto slot_of = [&](int step) { return lds + (step & (ex::kSlotsX - 1)) * G::kSlot; };
   auto begin_step = [&](int step) -> const uint8_t * {
-    if (step + 1 < nk) dma::wait_vmcnt<4>(); else dma::wait_vmcnt<0>();
+    if (step + 1 < nk) dma::wait_vmcnt<5>(); else dma::wait_vmcnt<0>();
     __syncthreads();
     if (step + 2 < nk) issue(step + 2);
     return slot_of(step);
@@ -646,8 +641,8 @@ __global__ __launch_bounds__(ex::kThreadsX, 1) void gemm_exact256x128_kernel(Spl
   // which step 3 fills only after the first two barriers: zero them (and
   // part is zero), so that it adds 0 x 0
   {
-    uint32_t *z = reinterpret_cast<uint32_t *>(lds_raw) + ((ex::kSlotsX - 1) * G::kSlot + kCodeA + kCodeB) / 4;
-    for (int e = t; e < (G::kScaleA + G::kScaleB) / 4; e += ex::kThreadsX) z[e] = 0u;
+    uint32_t *z = reinterpret_cast<uint32_t *>(lds_raw) + ((ex::kSlotsX - 1) * G::kSlot + 2 * ex::kCode) / 4;
+    for (int e = t; e < 2 * G::kScale / 4; e += ex::kThreadsX) z[e] = 0u;
   }
   issue(0);
   if (nk > 1) issue(1);
@@ -851,10 +846,10 @@ int launch_products_split(const Problem &pb, const uint8_t *ws, const Workspace 
   const int64_t items = pb.batch * pb.T * g.tiles_m * g.tiles_n;
   if (exact_split(pb)) {
     if (pb.scale_bytes == 4) {
-      const dim3 grid((unsigned)items), block(ex::kThreadsX);
-      if (pb.block == 16) hipLaunchKernelGGL(gemm_exact256x128_kernel<16>, grid, block, 0, st, g);
-      else if (pb.block == 32) hipLaunchKernelGGL(gemm_exact256x128_kernel<32>, grid, block, 0, st, g);
-      else hipLaunchKernelGGL(gemm_exact256x128_kernel<128>, grid, block, 0, st, g);
+      const dim3 grid((unsigned)(2 * items)), block(ex::kThreadsX);
+      if (pb.block == 16) hipLaunchKernelGGL(gemm_exact128x128_kernel<16>, grid, block, 0, st, g);
+      else if (pb.block == 32) hipLaunchKernelGGL(gemm_exact128x128_kernel<32>, grid, block, 0, st, g);
+      else hipLaunchKernelGGL(gemm_exact128x128_kernel<128>, grid, block, 0, st, g);
     } else {
       const dim3 grid((unsigned)items), block(kThreads);
       if (pb.block == 16) hipLaunchKernelGGL(gemm_dq256x128_kernel<16>, grid, block, 0, st, g);
