@@ -536,19 +536,19 @@ constexpr bool pair_n1() { return DEPTH == 1 && BS <= 32; }
 template <int DEPTH, int BS>
 constexpr int pair_threads() { return DEPTH == 2 ? 1024 : pair_n1<DEPTH, BS>() ? kB1NThreads : kB1Threads; }
 
-template <int DEPTH, int BS, bool F32>
+template <int DEPTH, int BS, bool F32, int CAP = 0>
 __global__ __launch_bounds__((pair_threads<DEPTH, BS>())) void encode_pair_kernel(Problem pb, PairArgs g) {
   constexpr bool N1 = pair_n1<DEPTH, BS>();
   constexpr int NT = pair_threads<DEPTH, BS>();
-  using TA = Tile<DEPTH, 16, 0>;
-  using TB = Tile<DEPTH, 16, 1, narrow_b(1, DEPTH, BS, 0) || N1>;
+  using TA = Tile<DEPTH, 16, 0, false, CAP>;
+  using TB = Tile<DEPTH, 16, 1, narrow_b(1, DEPTH, BS, 0) || N1, CAP>;
   __shared__ float4 lds4[(TA::lds_floats > TB::lds_floats ? TA::lds_floats : TB::lds_floats) / 4];
   float *lds = reinterpret_cast<float *>(lds4);
   if (blockIdx.x < g.tiles[0])
-    encode16_tile<0, DEPTH, BS, F32, 0, 0, false, NT>(lds, g.src[0], pb, g.cf[0], g.codes[0], g.scales[0], g.tiles_l[0],
+    encode16_tile<0, DEPTH, BS, F32, 0, CAP, false, NT>(lds, g.src[0], pb, g.cf[0], g.codes[0], g.scales[0], g.tiles_l[0],
                                                       nullptr, blockIdx.x, g.tiles[0], blockIdx.y);
   else
-    encode16_tile<1, DEPTH, BS, F32, 0, 0, N1, NT>(lds, g.src[1], pb, g.cf[1], g.codes[1], g.scales[1], g.tiles_l[1],
+    encode16_tile<1, DEPTH, BS, F32, 0, CAP, N1, NT>(lds, g.src[1], pb, g.cf[1], g.codes[1], g.scales[1], g.tiles_l[1],
                                                    nullptr, blockIdx.x - g.tiles[0], g.tiles[1], blockIdx.y);
 }
 
@@ -954,27 +954,27 @@ int launch_encode_noise(const Problem &pb, const DeviceTables &tab, const float 
 
 namespace {
 
-template <int DEPTH, int BS, bool F32>
+template <int DEPTH, int BS, bool F32, int CAP>
 hipError_t launch_pair(const Problem &pb, PairArgs &g, hipStream_t st) {
-  using TA = Tile<DEPTH, 16, 0>;
-  using TB = Tile<DEPTH, 16, 1, narrow_b(1, DEPTH, BS, 0) || pair_n1<DEPTH, BS>()>;
+  using TA = Tile<DEPTH, 16, 0, false, CAP>;
+  using TB = Tile<DEPTH, 16, 1, narrow_b(1, DEPTH, BS, 0) || pair_n1<DEPTH, BS>(), CAP>;
   auto tiles = [](int64_t n, int64_t t) { return (n + t - 1) / t; };
   g.tiles_l[0] = tiles(pb.kp, TA::TL);
   g.tiles_l[1] = tiles(pb.kp, TB::TL);
   g.tiles[0] = (unsigned)(g.tiles_l[0] * tiles(pb.mp, TA::TR));
   g.tiles[1] = (unsigned)(g.tiles_l[1] * tiles(pb.np, TB::TR));
   const dim3 grid(g.tiles[0] + g.tiles[1], (unsigned)pb.batch);
-  hipLaunchKernelGGL((encode_pair_kernel<DEPTH, BS, F32>), grid, dim3(pair_threads<DEPTH, BS>()), 0, st, pb, g);
+  hipLaunchKernelGGL((encode_pair_kernel<DEPTH, BS, F32, CAP>), grid, dim3(pair_threads<DEPTH, BS>()), 0, st, pb, g);
   return hipGetLastError();
 }
 
-template <int DEPTH>
+template <int DEPTH, int CAP = 0>
 hipError_t launch_pair_any(const Problem &pb, PairArgs &g, hipStream_t st) {
   const bool f32 = pb.rule == dev::RULE_FP32_AMAX;
   switch (pb.block) {
-    case 16: return f32 ? launch_pair<DEPTH, 16, true>(pb, g, st) : launch_pair<DEPTH, 16, false>(pb, g, st);
-    case 32: return f32 ? launch_pair<DEPTH, 32, true>(pb, g, st) : launch_pair<DEPTH, 32, false>(pb, g, st);
-    case 128: return f32 ? launch_pair<DEPTH, 128, true>(pb, g, st) : launch_pair<DEPTH, 128, false>(pb, g, st);
+    case 16: return f32 ? launch_pair<DEPTH, 16, true, CAP>(pb, g, st) : launch_pair<DEPTH, 16, false, CAP>(pb, g, st);
+    case 32: return f32 ? launch_pair<DEPTH, 32, true, CAP>(pb, g, st) : launch_pair<DEPTH, 32, false, CAP>(pb, g, st);
+    case 128: return f32 ? launch_pair<DEPTH, 128, true, CAP>(pb, g, st) : launch_pair<DEPTH, 128, false, CAP>(pb, g, st);
   }
   return hipErrorInvalidValue;
 }
@@ -984,10 +984,23 @@ hipError_t launch_pair_any(const Problem &pb, PairArgs &g, hipStream_t st) {
 // waves; us, separate / one launch, block 32: 134 MB 45.9 / 43.1, 157 MB 52.1 /
 // 48.1, 302 MB 87.9 / 91.9, 537 MB 143 / 154; block 128: 33 MB 20.5 / 19.0,
 // 134 MB 59.4 / 61.6).
+// Other shapes, on the sixteen-wave tiles over up to 16 blocks: always where
+// both sides stage them anyway (more than 8 blocks; <3,3,3;27> 5 MB 14.0 / 8.1,
+// 302 MB 186 / 180).  Grids of up to 8 blocks trade their wider depth-1 tiles
+// for it, whose few workgroups leave a small encode waiting (<2,2,3;11>, block
+// 128, fp32 scales: 3 MB 20.1 / 9.4, 21 MB 23.7 / 17.3, 25 MB 25.4 / 17.0, 42 MB
+// 27.1 / 27.6, 671 MB 313 / 423; block 32: 21 MB 24.4 / 15.6, 42 MB 27.1 / 24.9,
+// 84 MB 49.2 / 46.4, 168 MB 90.1 / 90.6, 671 MB 314 / 403; power-of-two scales
+// alike).
 bool one_launch(const Problem &pb) {
-  if (pb.shaped || pb.b_rows > 1 || pb.b_bf16 || pb.depth > 2) return false;
+  if (pb.b_rows > 1 || pb.b_bf16 || pb.depth > 2) return false;
   if (pb.depth == 2) return true;
   const int64_t bytes = 4 * pb.batch * (pb.M * pb.K + pb.K * pb.N);
+  if (pb.shaped) {
+    const int na = pb.gm * pb.gk, nb = pb.gk * pb.gn;
+    if (na > 16 || nb > 16) return false;
+    return (na > 8 && nb > 8) || bytes <= (pb.block == 128 ? int64_t(32) << 20 : int64_t(128) << 20);
+  }
   return bytes <= (pb.block == 128 ? int64_t(64) << 20 : int64_t(192) << 20);
 }
 
@@ -1003,6 +1016,7 @@ int launch_encode(const Problem &pb, const DeviceTables &tab, const float *A, co
     g.cf[0] = a_tab(tab); g.cf[1] = b_tab(tab);
     g.codes[0] = ws + wl.a_codes; g.codes[1] = ws + wl.b_codes;
     g.scales[0] = ws + wl.a_scales; g.scales[1] = ws + wl.b_scales;
+    if (pb.shaped) return launch_pair_any<2, 16>(pb, g, st);
     return pb.depth == 1 ? launch_pair_any<1>(pb, g, st) : launch_pair_any<2>(pb, g, st);
   }
   hipError_t e = launch_side<0>(pb, A, a_tab(tab), ws + wl.a_codes, ws + wl.a_scales, st);

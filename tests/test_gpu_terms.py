@@ -121,3 +121,33 @@ def test_encode_two_launches():
         c, s, bc, bs = half.operands()
         assert torch.equal(c, codes[:, :, h * i:h * (i + 1)]) and torch.equal(s, scales[:, :, h * i:h * (i + 1)])
         assert torch.equal(bc, bcodes) and torch.equal(bs, bscales)
+
+
+@pytest.mark.parametrize("block, rule, batch", [(128, "fp32_amax", 4), (32, "pow2_ceil", 14), (16, "fp32_amax", 14)])
+def test_shape_encode_launches(block, rule, batch):
+    """<2,2,3;12> batches past 32 MiB (block 128) and 128 MiB of operands take
+    one launch per side on the depth-1 tiles, their products alone one launch
+    for both on the sixteen-wave tiles: the same codes, scales and C."""
+    import numpy as np
+    import torch
+    import paper_2609_26077_amd as fm
+    from paper_2609_26077_amd.runner import FMM
+    U, V, W = np.zeros((12, 4)), np.zeros((12, 6)), np.zeros((12, 6))
+    for r in range(12):
+        i, j, l = r // 6, r // 3 % 2, r % 3
+        U[r, 2 * i + j] = V[r, 3 * j + l] = W[r, 2 * l + i] = 1.0
+    # a change of basis fills the rows, so that every block is combined
+    gauge = [np.array([[1.0, 0.3], [-0.2, 0.9]]), np.array([[0.8, -0.4], [0.1, 1.1]]),
+             np.array([[1.0, 0.2, -0.1], [0.3, 0.9, 0.2], [-0.2, 0.1, 1.2]])]
+    real = fm.fmm_realization_transform(fm.fmm_realization_create(U, V, W, shape=(2, 2, 3)), *gauge)
+    g = torch.Generator(device="cuda").manual_seed(9)
+    A = torch.randn((batch, 1024, 1024), generator=g, device="cuda")
+    B = torch.randn((batch, 1024, 1536), generator=g, device="cuda")
+    whole = FMM(real, batch, 1024, 1024, 1536, 1, block, rule)
+    C = whole.matmul(A, B)
+    ops = whole.operands()
+    alone = FMM(real, 1, 1024, 1024, 1536, 1, block, rule)
+    for b in (0, batch - 1):
+        Cb = alone.matmul(A[b:b + 1], B[b:b + 1])
+        assert torch.equal(Cb[0], C[b])
+        assert all(torch.equal(x[0], y[b]) for x, y in zip(alone.operands(), ops))
