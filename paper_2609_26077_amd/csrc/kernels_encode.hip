@@ -485,8 +485,8 @@ __device__ __forceinline__ void encode16_tile(float *lds, const float *__restric
       stored = sc.stored;
 #pragma unroll
       for (int j = 0; j < 4; ++j)
-        w[j] = dev::e4m3_pack4(__fdiv_rn(x[4 * j], sc.div), __fdiv_rn(x[4 * j + 1], sc.div),
-                               __fdiv_rn(x[4 * j + 2], sc.div), __fdiv_rn(x[4 * j + 3], sc.div));
+        w[j] = dev::e4m3_pack4(dev::div_by(x[4 * j], sc.div, sc.inv), dev::div_by(x[4 * j + 1], sc.div, sc.inv),
+                               dev::div_by(x[4 * j + 2], sc.div, sc.inv), dev::div_by(x[4 * j + 3], sc.div, sc.inv));
     } else {
       // a power-of-two rule (the ceiling or the OCP one)
       const dev::Scale sc = dev::block_scale(m, pb.rule == dev::RULE_POW2_CEIL ? dev::RULE_POW2_CEIL
@@ -581,8 +581,8 @@ __device__ __forceinline__ uint32_t quantize4(const Problem &pb, float m, float 
   if constexpr (F32) {
     const dev::Scale sc = dev::block_scale(m, dev::RULE_FP32_AMAX);
     stored = sc.stored;
-    return dev::e4m3_pack4(__fdiv_rn(x0, sc.div), __fdiv_rn(x1, sc.div), __fdiv_rn(x2, sc.div),
-                           __fdiv_rn(x3, sc.div));
+    return dev::e4m3_pack4(dev::div_by(x0, sc.div, sc.inv), dev::div_by(x1, sc.div, sc.inv), dev::div_by(x2, sc.div, sc.inv),
+                           dev::div_by(x3, sc.div, sc.inv));
   } else {
     const dev::Scale sc =
         dev::block_scale(m, pb.rule == dev::RULE_POW2_CEIL ? dev::RULE_POW2_CEIL : dev::RULE_POW2_OCP);

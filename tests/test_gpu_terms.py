@@ -151,3 +151,38 @@ def test_shape_encode_launches(block, rule, batch):
         Cb = alone.matmul(A[b:b + 1], B[b:b + 1])
         assert torch.equal(Cb[0], C[b])
         assert all(torch.equal(x[0], y[b]) for x, y in zip(alone.operands(), ops))
+
+
+@pytest.mark.parametrize("depth, block", [(1, 16), (1, 128), (2, 32), (3, 32)])
+@pytest.mark.parametrize("exponent", [-30, 0, 100])
+def test_fp32_scale_quotients(depth, block, exponent):
+    """fp32 scales, numerators within 4 ulp of every boundary between two codes
+    times the scale, signed, zeros of both signs and subnormals among them:
+    the codes of the correctly rounded quotient (numpy's division), exactly."""
+    import numpy as np
+    import torch
+    from paper_2609_26077_amd.runner import FMM
+    rng = np.random.RandomState(11)
+    n, rows, kp = 1 << depth, 64, 1024
+    nb = kp // block
+    amax = np.ldexp(rng.uniform(1, 2, (rows, nb, 1)), exponent).astype(np.float32)
+    s = amax / np.float32(448)
+    tie = np.concatenate([np.arange(17, 32, 2) / 16 * 2.0 ** e for e in range(-6, 9)] + [np.arange(1, 16, 2) * 2.0 ** -10])
+    x = (rng.choice(tie, (rows, nb, block)) * s).astype(np.float32)
+    x = (x.view(np.int32) + rng.randint(-4, 5, x.shape).astype(np.int32)).view(np.float32)
+    x = np.minimum(x, amax) * rng.choice([-1, 1], x.shape).astype(np.float32)
+    x[:, :, 1] = 0.0
+    x[:, :, 2] = -0.0
+    x[:, :, 3] = np.float32(1e-45)
+    x[:, :, 4] = np.float32(-1e-45)
+    x[:, :, 0] = amax[:, :, 0]
+    want = torch.from_numpy(np.clip(x / s, np.float32(-448), np.float32(448))).to(torch.float8_e4m3fn).view(torch.uint8)
+    want = want.reshape(rows, kp).numpy()
+    # the cubic algorithm's terms are the sub-blocks themselves: all alike
+    A = torch.from_numpy(np.ascontiguousarray(np.tile(x.reshape(rows, kp), (n, n))))[None].cuda()
+    B = torch.from_numpy(np.ascontiguousarray(np.tile(x.reshape(rows, kp).T, (n, n))))[None].cuda()
+    f = FMM("cubic8", 1, n * rows, n * kp, n * rows, depth, block, "fp32_amax")
+    f.encode(A, B)
+    for codes, scales in (f.operands()[:2], f.operands()[2:]):
+        assert (scales.cpu().numpy() == s[..., 0]).all()
+        assert (codes.cpu().numpy() == want).all()
