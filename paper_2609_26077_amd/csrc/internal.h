@@ -112,8 +112,45 @@ struct Workspace {
   size_t b_amax;     // FMM_FLAG_B_BLOCK128 plans: 2-D block maxima [batch][T][ceil(n'/128)][kblocks] u32
 };
 
+// Depth-3 encoder: the inner digit's sign and magnitude pattern of a side's
+// coefficients.  For one group of R terms (the outer digits fixed) and one outer
+// block, column c of the inner 2 x 2 grid gives the terms coefficients that fall
+// into at most two classes of one magnitude; a term's product fl32(c a) is then
+// the same, up to its sign, for all terms of a class.  Pattern 1 is T*'s,
+// pattern 2 Strassen's (both sides of either have the same seven rows, in another
+// order: EncodePattern::perm).  Bit j of a mask is pattern row j; a class's
+// lowest row leads it (rows 0, 1 and 4 lead all of them).
+struct EncodePattern {
+  int id;               // 0: neither (or not depth 3)
+  int32_t perm[8];      // inner digit of pattern row j
+};
+constexpr int kPatternRows = 7;
+constexpr unsigned pattern_members(int id, int col, int cls) {
+  if (id == 1) {
+    if (cls == 0) return col == 0 ? 0x25u : col == 1 ? 0x50u : col == 2 ? 0x2eu : 0x0bu;
+    return col == 1 ? 0u : 0x50u;
+  }
+  if (cls == 0) return col == 0 ? 0x35u : col == 1 ? 0x50u : col == 2 ? 0x22u : 0x4bu;
+  return 0u;
+}
+// the members whose sign is the opposite of the leader's
+constexpr unsigned pattern_minus(int id, int col, int cls) {
+  if (id == 1) {
+    if (cls == 0) return col == 0 ? 0x20u : col == 2 ? 0x08u : 0u;
+    return col == 0 || col == 3 ? 0x40u : 0u;
+  }
+  return col == 0 ? 0x20u : col == 3 ? 0x40u : 0u;
+}
+constexpr int pattern_lead(int id, int col, int cls) {
+  const unsigned m = pattern_members(id, col, cls);
+  return m & 1u ? 0 : m & 2u ? 1 : 4;
+}
+// the pattern that a side's depth-3 table (T x 64) follows, from its base rows (R x 4)
+EncodePattern encode_pattern(int R, const float *base, const float *flat);
+
 // Device copies of the plan's tables (one allocation).
 struct DeviceTables {
+  EncodePattern u_pat, v_pat;  // (host values; depth 3)
   const int32_t *a_off;        // T + 1
   const CoefEntry *a_ent;
   const int32_t *b_off;

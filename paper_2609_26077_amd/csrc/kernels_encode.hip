@@ -36,9 +36,10 @@ struct SideTab {
   const int32_t *off;
   const CoefEntry *ent;
   const float *dense;
+  EncodePattern pat;     // depth 3
 };
-inline SideTab a_tab(const DeviceTables &t) { return {t.a_off, t.a_ent, t.u_dense}; }
-inline SideTab b_tab(const DeviceTables &t) { return {t.b_off, t.b_ent, t.v_dense}; }
+inline SideTab a_tab(const DeviceTables &t) { return {t.a_off, t.a_ent, t.u_dense, t.u_pat}; }
+inline SideTab b_tab(const DeviceTables &t) { return {t.b_off, t.b_ent, t.v_dense, t.v_pat}; }
 
 // The coefficient of block b of a dense row spread one block per lane (b uniform).
 __device__ __forceinline__ float lane_coef(float c, int b) {
@@ -591,9 +592,33 @@ __device__ __forceinline__ uint32_t quantize4(const Problem &pb, float m, float 
   }
 }
 
+// One block's contributions to the seven terms of a group whose inner column
+// COL follows pattern PAT: each class's product once, then one addition or
+// subtraction a term, as x + fl32(c a) has it bit for bit (c's sign moves
+// through the product and the sum exactly).
+template <int PAT, int COL>
+__device__ __forceinline__ void add_column(float (&x)[8][4], const float4 &v, const float (&c)[8], int b) {
+#pragma unroll
+  for (int cls = 0; cls < 2; ++cls) {
+    if (pattern_members(PAT, COL, cls) == 0) continue;
+    const float cb = lane_coef(c[pattern_lead(PAT, COL, cls)], b);
+    const float p0 = __fmul_rn(cb, v.x), p1 = __fmul_rn(cb, v.y), p2 = __fmul_rn(cb, v.z), p3 = __fmul_rn(cb, v.w);
+#pragma unroll
+    for (int j = 0; j < kPatternRows; ++j) {
+      if (!(pattern_members(PAT, COL, cls) >> j & 1)) continue;
+      const bool minus = pattern_minus(PAT, COL, cls) >> j & 1;
+      x[j][0] = minus ? __fsub_rn(x[j][0], p0) : __fadd_rn(x[j][0], p0);
+      x[j][1] = minus ? __fsub_rn(x[j][1], p1) : __fadd_rn(x[j][1], p1);
+      x[j][2] = minus ? __fsub_rn(x[j][2], p2) : __fadd_rn(x[j][2], p2);
+      x[j][3] = minus ? __fsub_rn(x[j][3], p3) : __fadd_rn(x[j][3], p3);
+    }
+  }
+}
+
 constexpr bool narrow_b3(int side, int bs) { return side == 1 && bs <= 256 / kB3Rows; }
 
-template <int SIDE, int BS, bool F32, bool GEN = false>
+// PAT: the side's coefficients follow that EncodePattern (0: any coefficients).
+template <int SIDE, int BS, bool F32, bool GEN = false, int PAT = 0>
 __global__ __launch_bounds__((Tile<3, 4, SIDE, narrow_b3(SIDE, BS)>::threads), 8) void encode4_kernel(
     const float *__restrict__ src, Problem pb, SideTab cf, uint8_t *__restrict__ codes, uint8_t *__restrict__ scales,
     int64_t tiles_l) {
@@ -645,7 +670,64 @@ __global__ __launch_bounds__((Tile<3, 4, SIDE, narrow_b3(SIDE, BS)>::threads), 8
   const int64_t nfull = ((T + G - 1) / G / WSTEP) * WSTEP;      // groups taken in whole rounds
   const int64_t tail0 = nfull * G < T ? nfull * G : T;          // the first term taken alone
   const int64_t units = nfull + (T - tail0);
-  for (int64_t u = wave; u < units; u += WSTEP) {
+  int64_t u = wave;
+  if constexpr (PAT != 0) {
+    // Whole rounds under a known pattern: a group's terms draw on an outer
+    // block all or none, and its two inner blocks of one inner row sit side by
+    // side, so the walk in ascending block order needs no test per term, and a
+    // product shared by a class's terms is formed once: per outer block
+    // 7 x 4 multiplications and 18 x 4 additions for T* (4 x 4 and 12 x 4 for
+    // Strassen) against 18 x 8 operations and 28 tests (12 x 8).  The arithmetic
+    // bounds this kernel (us, 8192^3: T* 1066 -> 778, Strassen 679 -> 559; T*
+    // 16384x8192x16384 2035 -> 1430, 2048x7168x2048 274 -> 174; codes identical).
+    for (; u < nfull; u += WSTEP) {
+      const int64_t g0 = u * kPatternRows;
+      float c[kG];
+#pragma unroll
+      for (int j = 0; j < kG; ++j) c[j] = 0.0f;
+#pragma unroll
+      for (int j : {0, 1, 4}) c[j] = cf.dense[(g0 + cf.pat.perm[j]) * 64 + lane];
+      // outer blocks in use: row 0 has the inner corner block in both patterns
+      const uint64_t outer = __ballot(c[0] != 0.0f);
+      float x[kG][4];
+#pragma unroll
+      for (int j = 0; j < kG; ++j) x[j][0] = x[j][1] = x[j][2] = x[j][3] = -0.0f;
+      // block b = 16 P + 8 p + 2 Q + q of outer rows P, outer columns Q, inner (p, q)
+      for (int P = 0; P < 4; ++P) {
+        const uint32_t qs = (uint32_t)(outer >> (16 * P)) & 0x55u;
+        uint32_t rest = qs;
+        while (rest != 0) {
+          const int b = 16 * P + __builtin_ctz(rest);
+          rest &= rest - 1;
+          const float *pv = lrow + b * (TR * STR);
+          const float4 v0 = *reinterpret_cast<const float4 *>(pv), v1 = *reinterpret_cast<const float4 *>(pv + TR * STR);
+          add_column<PAT, 0>(x, v0, c, b);
+          add_column<PAT, 1>(x, v1, c, b + 1);
+        }
+        rest = qs;
+        while (rest != 0) {
+          const int b = 16 * P + 8 + __builtin_ctz(rest);
+          rest &= rest - 1;
+          const float *pv = lrow + b * (TR * STR);
+          const float4 v0 = *reinterpret_cast<const float4 *>(pv), v1 = *reinterpret_cast<const float4 *>(pv + TR * STR);
+          add_column<PAT, 2>(x, v0, c, b);
+          add_column<PAT, 3>(x, v1, c, b + 1);
+        }
+      }
+#pragma unroll
+      for (int j = 0; j < kPatternRows; ++j) {
+        if (outer == 0) x[j][0] = x[j][1] = x[j][2] = x[j][3] = 0.0f;
+        const float mx = __uint_as_float(group_max_bits<GL>(__float_as_uint(
+            fmaxf(fmaxf(fabsf(x[j][0]), fabsf(x[j][1])), fmaxf(fabsf(x[j][2]), fabsf(x[j][3]))))));
+        uint32_t stored;
+        const uint32_t w = quantize4<F32>(pb, mx, x[j][0], x[j][1], x[j][2], x[j][3], stored);
+        const int64_t plane = bt * T + g0 + cf.pat.perm[j];      // uniform
+        if (o_valid) *reinterpret_cast<uint32_t *>(codes + plane * code_plane + o_code) = w;
+        if (o_leader) store_scale(pb, scales, plane * scale_plane + o_scale, stored);
+      }
+    }
+  }
+  for (; u < units; u += WSTEP) {
     const int64_t g0 = u < nfull ? u * G : tail0 + (u - nfull);
     const int gn = u < nfull ? (int)(T - g0 < G ? T - g0 : G) : 1;
     float c[kG];
@@ -780,35 +862,40 @@ hipError_t launch_wide(const Problem &pb, const float *src, const SideTab &cf,
 }
 
 // 4 positions per lane over a grid of up to 64 blocks (depth 3, or GEN)
+template <int SIDE, int BS, bool GEN>
+hipError_t launch4(const Problem &pb, const float *src, const SideTab &cf, uint8_t *codes, uint8_t *scales, hipStream_t st) {
+  using TT = Tile<3, 4, SIDE, narrow_b3(SIDE, BS)>;
+  const int64_t rows = SIDE == 0 ? pb.mp : pb.np;
+  const int64_t tiles_l = (pb.kp + TT::TL - 1) / TT::TL;
+  const int64_t tiles_r = (rows + TT::TR - 1) / TT::TR;
+  const dim3 grid((unsigned)(tiles_l * tiles_r), (unsigned)pb.batch), blk(TT::threads);
+  const bool f32 = pb.rule == dev::RULE_FP32_AMAX;
+#define FMM_ENCODE4(F32, PAT) \
+  hipLaunchKernelGGL((encode4_kernel<SIDE, BS, F32, GEN, PAT>), grid, blk, 0, st, src, pb, cf, codes, scales, tiles_l)
+  if constexpr (!GEN) {
+    if (cf.pat.id != 0) {
+      if (cf.pat.id == 1 && f32) FMM_ENCODE4(true, 1);
+      else if (cf.pat.id == 1) FMM_ENCODE4(false, 1);
+      else if (f32) FMM_ENCODE4(true, 2);
+      else FMM_ENCODE4(false, 2);
+      return hipGetLastError();
+    }
+  }
+  if (f32) FMM_ENCODE4(true, 0);
+  else FMM_ENCODE4(false, 0);
+#undef FMM_ENCODE4
+  return hipGetLastError();
+}
+
 template <int SIDE, bool GEN = false>
 hipError_t launch_narrow4(const Problem &pb, const float *src, const SideTab &cf,
                           uint8_t *codes, uint8_t *scales, hipStream_t st) {
-  const int64_t rows = SIDE == 0 ? pb.mp : pb.np;
-  // the B side's tile at blocks <= 256 / kB3Rows (its narrow form), else the common one
-  const bool nar = SIDE == 1 && pb.block <= 256 / kB3Rows;
-  const int TL = nar ? Tile<3, 4, 1, true>::TL : kTL, TR = nar ? Tile<3, 4, 1, true>::TR : Tile<3, 4, SIDE>::TR;
-  const int64_t tiles_l = (pb.kp + TL - 1) / TL;
-  const int64_t tiles_r = (rows + TR - 1) / TR;
-  const dim3 grid((unsigned)(tiles_l * tiles_r), (unsigned)pb.batch);
-  const bool f32 = pb.rule == dev::RULE_FP32_AMAX;
-  const dim3 blk(Tile<3, 4, SIDE>::threads);
   switch (pb.block) {
-    case 16:
-      if (f32) hipLaunchKernelGGL((encode4_kernel<SIDE, 16, true, GEN>), grid, blk, 0, st, src, pb, cf, codes, scales, tiles_l);
-      else hipLaunchKernelGGL((encode4_kernel<SIDE, 16, false, GEN>), grid, blk, 0, st, src, pb, cf, codes, scales, tiles_l);
-      break;
-    case 32:
-      if (f32) hipLaunchKernelGGL((encode4_kernel<SIDE, 32, true, GEN>), grid, blk, 0, st, src, pb, cf, codes, scales, tiles_l);
-      else hipLaunchKernelGGL((encode4_kernel<SIDE, 32, false, GEN>), grid, blk, 0, st, src, pb, cf, codes, scales, tiles_l);
-      break;
-    case 128:
-      if (f32) hipLaunchKernelGGL((encode4_kernel<SIDE, 128, true, GEN>), grid, blk, 0, st, src, pb, cf, codes, scales, tiles_l);
-      else hipLaunchKernelGGL((encode4_kernel<SIDE, 128, false, GEN>), grid, blk, 0, st, src, pb, cf, codes, scales, tiles_l);
-      break;
-    default:
-      return hipErrorInvalidValue;
+    case 16: return launch4<SIDE, 16, GEN>(pb, src, cf, codes, scales, st);
+    case 32: return launch4<SIDE, 32, GEN>(pb, src, cf, codes, scales, st);
+    case 128: return launch4<SIDE, 128, GEN>(pb, src, cf, codes, scales, st);
   }
-  return hipGetLastError();
+  return hipErrorInvalidValue;
 }
 
 template <int SIDE>

@@ -218,6 +218,13 @@ int fmm_plan_create(const fmm_real *d, const fmm_plan_desc *desc, fmm_plan **out
   boff[T] = (int32_t)bent.size();
   std::vector<float> wbase((size_t)fmm::kMaxRank * 4, 0.0f);
   if (!shaped) fmm_realization_tables(d, 1, nullptr, nullptr, wbase.data());
+  fmm::EncodePattern upat = {}, vpat = {};
+  if (!shaped && q.depth == 3 && R == fmm::kPatternRows) {
+    std::vector<float> u1((size_t)R * 4), v1((size_t)R * 4);
+    fmm_realization_tables(d, 1, u1.data(), v1.data(), nullptr);
+    upat = fmm::encode_pattern((int)R, u1.data(), U.data());
+    vpat = fmm::encode_pattern((int)R, v1.data(), V.data());
+  }
   std::vector<float> wouter;
   if (q.depth >= 2) {
     const int no = 1 << (2 * (q.depth - 1));
@@ -289,6 +296,8 @@ int fmm_plan_create(const fmm_real *d, const fmm_plan_desc *desc, fmm_plan **out
   p->tab.w_full = reinterpret_cast<const float *>(base + s_aoff + s_boff + s_aent + s_bent + s_wi + s_wo);
   p->tab.u_dense = reinterpret_cast<const float *>(base + o_ud);
   p->tab.v_dense = reinterpret_cast<const float *>(base + o_ud + s_ud);
+  p->tab.u_pat = upat;
+  p->tab.v_pat = vpat;
   *out = p;
   return FMM_OK;
 }

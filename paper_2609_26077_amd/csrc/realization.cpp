@@ -246,6 +246,65 @@ void flatten(const double (*base)[4], int R, int depth, float *out) {
   }
 }
 
+// Pattern rows taken in order, each matched to an unused base row (depth first).
+static bool match_rows(int id, const float *base, int j, unsigned used, int32_t *perm) {
+  if (j == kPatternRows) return true;
+  for (int r = 0; r < kPatternRows; ++r) {
+    if (used >> r & 1) continue;
+    perm[j] = r;
+    bool ok = true;
+    for (int col = 0; col < 4 && ok; ++col) {
+      const float v = base[4 * r + col];
+      bool member = false;
+      for (int cls = 0; cls < 2; ++cls) {
+        if (!(pattern_members(id, col, cls) >> j & 1)) continue;
+        member = true;
+        const float lead = base[4 * perm[pattern_lead(id, col, cls)] + col];   // (a leader is its class's first row)
+        ok = v != 0.0f && v == (pattern_minus(id, col, cls) >> j & 1 ? -lead : lead);
+      }
+      if (!member) ok = v == 0.0f;
+    }
+    if (ok && match_rows(id, base, j + 1, used | 1u << r, perm)) return true;
+  }
+  return false;
+}
+
+EncodePattern encode_pattern(int R, const float *base, const float *flat) {
+  EncodePattern p = {};
+  if (R != kPatternRows) return p;
+  for (int id = 1; id <= 2; ++id) {
+    if (!match_rows(id, base, 0, 0u, p.perm)) continue;
+    // the flattened entries themselves: a class's magnitudes equal bit for bit,
+    // an outer block zero for all of a group's terms or for none (products
+    // that round to zero would break either)
+    bool ok = true;
+    for (int g = 0; g < R * R && ok; ++g) {
+      const float *rows = flat + (int64_t)g * R * 64;
+      for (int b = 0; b < 64 && ok; ++b) {
+        const int col = ((b >> 3) & 1) * 2 + (b & 1);
+        const bool outer = rows[64 * p.perm[0] + (b & ~9)] != 0.0f;
+        for (int j = 0; j < kPatternRows && ok; ++j) {
+          const float v = rows[64 * p.perm[j] + b];
+          float want = 0.0f;
+          for (int cls = 0; cls < 2; ++cls) {
+            if (!outer || !(pattern_members(id, col, cls) >> j & 1)) continue;
+            const float lead = rows[64 * p.perm[pattern_lead(id, col, cls)] + b];
+            want = pattern_minus(id, col, cls) >> j & 1 ? -lead : lead;
+            ok = lead != 0.0f;
+          }
+          ok = ok && v == want;
+        }
+      }
+    }
+    if (ok) {
+      p.id = id;
+      return p;
+    }
+  }
+  p.id = 0;
+  return p;
+}
+
 // ---- other shapes <m,k,n;R> ------------------------------------------------
 // U_r indexed i k + j (A block (i, j)), V_r j n + l (B block (j, l)), W_r
 // l m + i (C block (i, l), the cyclic third factor of the <2,2,2> case).

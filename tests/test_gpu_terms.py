@@ -186,3 +186,46 @@ def test_fp32_scale_quotients(depth, block, exponent):
     for codes, scales in (f.operands()[:2], f.operands()[2:]):
         assert (scales.cpu().numpy() == s[..., 0]).all()
         assert (codes.cpu().numpy() == want).all()
+
+
+@pytest.mark.parametrize("block, rule", [(32, "pow2_ceil"), (16, "fp32_amax"), (128, "pow2_ocp")])
+@pytest.mark.parametrize("change", ["none", "order", "sign", "pair", "magnitude", "half"])
+@pytest.mark.parametrize("name", ["strassen", "tstar"])
+def test_depth3_patterns(name, change, block, rule):
+    """The depth-3 encoder by its tables' sign and magnitude pattern: T* and
+    Strassen, their terms in another order, and tables that miss the patterns
+    by one term's sign, two terms' signs, a magnitude, or (halved on one
+    side, doubled on the other) by an exact power of two: codes and scales
+    against the oracle's."""
+    import numpy as np
+    import torch
+    import fmm_inputs as gen
+    import paper_2609_26077_amd as fm
+    from oracle import e4m3, fmm
+    from paper_2609_26077_amd.runner import FMM
+    U, V, W = fm.fmm_realization_coefficients(fm.fmm_realization_builtin(name))
+    if change == "order":
+        p = [4, 6, 0, 2, 1, 5, 3]
+        U, V, W = U[p], V[p], W[p]
+    elif change == "sign":
+        U[5], W[5] = -U[5], -W[5]
+    elif change == "pair":
+        for r in (1, 6):
+            U[r], V[r] = -U[r], -V[r]
+    elif change == "magnitude":
+        U[2], V[2] = 3 * U[2], V[2] / 3
+    elif change == "half":
+        U[0], V[0] = U[0] / 2, 2 * V[0]
+    real = fm.fmm_realization_create(U, V, W)
+    M, K, N = 8 * 18, 8 * 160 if block < 128 else 8 * 256, 8 * 10
+    A, B = gen.operands("gaussian", 1, M, K, N, seed=0, cfg=37)
+    A[0, 5] = 0.0
+    f = FMM(real, 1, M, K, N, 3, block, rule)
+    f.encode(torch.from_numpy(A).cuda(), torch.from_numpy(B).cuda())
+    ac, asc, bc, bsc = [t.cpu().numpy()[0] for t in f.operands()]
+    rules = {"fp32_amax": e4m3.RULE_FP32_AMAX, "pow2_ceil": e4m3.RULE_POW2_CEIL, "pow2_ocp": e4m3.RULE_POW2_OCP}
+    tables = fm.fmm_realization_tables(real, 3)
+    for side, X, T, codes, scales in (("A", A[0], tables[0], ac, asc), ("B", B[0], tables[1], bc, bsc)):
+        e = fmm.encode_side(X, T, 3, block, rules[rule], side)
+        assert np.array_equal(codes, e["codes"]), side
+        assert np.array_equal(scales, e["scales"]), side
