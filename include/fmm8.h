@@ -102,7 +102,7 @@ enum {
    * of the contracted axis, its maximum taken over the encoded combination;
    * the last block of a ragged N / 2 is short.  The stored scales stay one per
    * (row, block), replicated over each 128-row block.  Depth 1 only
-   * (FMM_ERR_UNSUPPORTED otherwise).  The encoder reads B twice. */
+   * (FMM_ERR_UNSUPPORTED otherwise). */
   FMM_FLAG_B_BLOCK128 = 2,
   /* Round each encoded B combination to bfloat16 (nearest, ties to even)
    * before its scale and cast (Appendix E: the real path's pre-round of the
@@ -291,8 +291,8 @@ int fmm_plan_create(const fmm_real *d, const fmm_plan_desc *desc, fmm_plan **out
 
 /* Bytes of device workspace fmm_encode/fmm_multiply/fmm_matmul need: the
  * codes and scales of both operands, plus, for large-tile plans the fp32
- * sub-products P_r, for the others at depth >= 2 the inner-level partial
- * products, and with FMM_FLAG_B_BLOCK128 the B side's 2-D block maxima.
+ * sub-products P_r, and for the others at depth >= 2 the inner-level partial
+ * products.
  * The workspace must be 256-byte aligned. */
 int fmm_plan_workspace_size(const fmm_plan *p, size_t *bytes);
 

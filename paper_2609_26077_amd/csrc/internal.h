@@ -109,7 +109,6 @@ inline int64_t scale_plane_bytes(const Problem &pb, int64_t rows) {
 struct Workspace {
   size_t a_codes, b_codes, a_scales, b_scales, partial, total;
   size_t products;   // split plans only: the fp32 sub-products P_r
-  size_t b_amax;     // FMM_FLAG_B_BLOCK128 plans: 2-D block maxima [batch][T][ceil(n'/128)][kblocks] u32
 };
 
 // Depth-3 encoder: the inner digit's sign and magnitude pattern of a side's

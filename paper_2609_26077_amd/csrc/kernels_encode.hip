@@ -265,16 +265,9 @@ __device__ __forceinline__ void store_scale(const Problem &pb, uint8_t *scales, 
 // B 32 rows (four waves per term, two terms at once); depth 2 one wave per
 // term, sixteen terms at once.
 // ---------------------------------------------------------------------------
-// Weight-side deployment granularity (FMM_FLAG_B_BLOCK128 / FMM_FLAG_B_BF16,
-// B side at depth 1), in two launches over the same tiles:
-//   MODE 1: combine (and round to bfloat16), then the maximum of |y| over the
-//           block's positions and the wave's 8 rows, merged into the 2-D
-//           block's maximum amax[bt][r][row block][kb] by an integer atomic
-//           maximum on the float bits (non-negative, so the order of the
-//           merges does not matter); nothing else is stored;
-//   MODE 2: combine (and round), take the block maximum from amax (or, with
-//           1-row blocks, from the lanes as in MODE 0), scale, cast, store.
 // MODE 0 is the plain encoder.
+// MODE 2 (FMM_FLAG_B_BF16 without FMM_FLAG_B_BLOCK128, B side at depth 1) rounds
+// the combinations to bfloat16 first.
 // MODE 3 measures the operand-side rounding energy of an encoding already in
 // the workspace (Appendix D, eq. D.1): it forms x_r exactly as the encoder
 // does, decodes the stored codes and scales to xhat_r (exact in binary64),
@@ -299,10 +292,9 @@ template <int SIDE, int DEPTH, int BS, bool F32, int MODE, int CAP, bool N1, int
 __device__ __forceinline__ void encode16_tile(float *lds, const float *__restrict__ src, const Problem &pb, const SideTab &cf,
                                               uint8_t *__restrict__ codes, uint8_t *__restrict__ scales, int64_t tiles_l,
                                               void *__restrict__ aux, unsigned bx, unsigned nbx, int64_t bt) {
-  static_assert(MODE == 0 || MODE == 3 || (SIDE == 1 && DEPTH == 1), "deployment granularity: B side, depth 1");
+  static_assert(MODE == 0 || MODE == 3 || (MODE == 2 && SIDE == 1 && DEPTH == 1), "bfloat16 combinations: B side, depth 1");
   static_assert(CAP == 0 || (MODE == 0 && (DEPTH == 1 || CAP == 16)), "other shapes: the plain encoder");
   constexpr bool GEN = CAP != 0;
-  uint32_t *amax = reinterpret_cast<uint32_t *>(aux);
   using TT = Tile<DEPTH, 16, SIDE, narrow_b(SIDE, DEPTH, BS, MODE) || N1, CAP>;
   constexpr int TR = TT::TR, NB = TT::nblk, TL = TT::TL, STR = TT::stride;
   constexpr int RPW = 64 * 16 / TL;         // rows per wave: 8, or 16 in the narrow tile
@@ -441,43 +433,22 @@ __device__ __forceinline__ void encode16_tile(float *lds, const float *__restric
       }
       continue;
     }
-    if constexpr (MODE == 1 || MODE == 2) {
-      if (pb.b_bf16) {
+    if constexpr (MODE == 2) {
 #pragma unroll
-        for (int i = 0; i < 16; ++i) x[i] = bf16_round(x[i]);
-      }
+      for (int i = 0; i < 16; ++i) x[i] = bf16_round(x[i]);
     }
     // block maximum: the lane's 16, then across the lanes of its block
     float m = fmaxf(fabsf(x[0]), fabsf(x[1]));
 #pragma unroll
     for (int i = 2; i < 16; ++i) m = fmaxf(m, fabsf(x[i]));
-    // the 2-D block of this lane: row block (row0 + row) / 128 (a tile's rows
-    // lie in one), K block of position l0 + 16 ch
-    const int64_t kb = (l0 + 16 * ch) / pb.block;
-    const int64_t aidx = (((int64_t)bt * T + r) * ((rows + 127) / 128) + row0 / 128) * pb.kblocks + kb;
-    if constexpr (MODE == 1) {
-      // over the wave's 8 rows (lane bits 2..4), then the block's lanes
-      m = fmaxf(m, __shfl_xor(m, 4, 64));
-      m = fmaxf(m, __shfl_xor(m, 8, 64));
-      m = fmaxf(m, __shfl_xor(m, 16, 64));
-    }
-    if (MODE != 2 || pb.b_rows == 1) {
-      if (BS >= 32) {
-        uint32_t mb = __float_as_uint(m);                       // m >= 0
-        mb = max(mb, dpp_u<0xB1>(mb));                          // quad_perm [1, 0, 3, 2]
-        if (BS == 128) {
-          mb = max(mb, dpp_u<0x4E>(mb));                        // quad_perm [2, 3, 0, 1]
-          mb = max(mb, (uint32_t)__shfl_xor((int)mb, 32, 64));
-        }
-        m = __uint_as_float(mb);
+    if (BS >= 32) {
+      uint32_t mb = __float_as_uint(m);                       // m >= 0
+      mb = max(mb, dpp_u<0xB1>(mb));                          // quad_perm [1, 0, 3, 2]
+      if (BS == 128) {
+        mb = max(mb, dpp_u<0x4E>(mb));                        // quad_perm [2, 3, 0, 1]
+        mb = max(mb, (uint32_t)__shfl_xor((int)mb, 32, 64));
       }
-    }
-    if constexpr (MODE == 1) {
-      if (((lane >> 2) & 7) == 0 && lead && l0 + 16 * ch < pb.kp) atomicMax(amax + aidx, __float_as_uint(m));
-      continue;
-    }
-    if constexpr (MODE == 2) {
-      if (pb.b_rows > 1) m = o.valid ? __uint_as_float(amax[aidx]) : 0.0f;
+      m = __uint_as_float(mb);
     }
     uint32_t w[4];
     uint32_t stored;
@@ -795,10 +766,10 @@ __global__ __launch_bounds__((Tile<3, 4, SIDE, narrow_b3(SIDE, BS)>::threads), 8
 // workgroups share a CU (8192^3 T* encode 149 -> 143.5 us, codes identical).
 template <int SIDE, int DEPTH, int BS, bool F32, int MODE = 0, int CAP = 0, bool N1 = false>
 hipError_t launch16(const Problem &pb, const float *src, const SideTab &cf,
-                    uint8_t *codes, uint8_t *scales, hipStream_t st, void *amax = nullptr) {
+                    uint8_t *codes, uint8_t *scales, hipStream_t st, void *aux = nullptr) {
   if constexpr (SIDE == 1 && DEPTH == 1 && MODE == 0 && CAP == 0 && BS <= 32 && !N1) {
     if (pb.layout == FMM_LAYOUT_TILE256x64)
-      return launch16<SIDE, DEPTH, BS, F32, MODE, CAP, true>(pb, src, cf, codes, scales, st, amax);
+      return launch16<SIDE, DEPTH, BS, F32, MODE, CAP, true>(pb, src, cf, codes, scales, st, aux);
   }
   using TT = Tile<DEPTH, 16, SIDE, narrow_b(SIDE, DEPTH, BS, MODE) || N1, CAP>;
   const int64_t rows = SIDE == 0 ? pb.mp : pb.np;
@@ -806,42 +777,122 @@ hipError_t launch16(const Problem &pb, const float *src, const SideTab &cf,
   const int64_t tiles_r = (rows + TT::TR - 1) / TT::TR;
   const dim3 grid((unsigned)(tiles_l * tiles_r), (unsigned)pb.batch);
   hipLaunchKernelGGL((encode16_kernel<SIDE, DEPTH, BS, F32, MODE, CAP, N1>), grid, dim3(TT::threads), 0, st, src, pb, cf,
-                     codes, scales, tiles_l, amax);
+                     codes, scales, tiles_l, aux);
   return hipGetLastError();
 }
 
-__global__ __launch_bounds__(256) void zero_u32_kernel(uint32_t *p, int64_t n) {
-  for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256) p[i] = 0u;
+// ---------------------------------------------------------------------------
+// B side with 128-row scale blocks (FMM_FLAG_B_BLOCK128, depth 1), optionally of
+// bfloat16-rounded combinations (FMM_FLAG_B_BF16).
+//
+// A scale covers 128 columns of B x `block` positions, so a workgroup holds the
+// four sub-blocks' 128 columns x TL positions (TL = 128 at block 128, else 64) in
+// registers: a thread has 16 positions of one column of each (64 values; 256 KB a
+// workgroup at block 128, more than LDS), read once, a wave's load one 256-byte
+// row segment.  Per term every wave reduces the maximum of its 64 columns x 16
+// positions, the workgroup's waves meet at one barrier (the maxima's slots
+// alternate by term, so no second one is needed), and each thread quantizes its
+// run.  HBM bounds it, and at block 128 the one workgroup a CU holds, which loads
+// and computes in turn.  Two passes over B, the first for the maxima alone, and
+// a pass clearing these took (encode of both sides, us, before / now): 8192^3
+// fp32 scales at block 128 230 / 196, power-of-two scales at block 128 224 / 165, at
+// block 32 223 / 147; 4096^3 block 128 69.5 / 49.7; 512^3 block 128 23.1 / 22.9.
+// ---------------------------------------------------------------------------
+template <int BS>
+constexpr int rows128_tl() { return BS == 128 ? 128 : 64; }
+
+template <int BS, bool F32>
+__global__ __launch_bounds__(8 * rows128_tl<BS>(), 4) void encode_rows128_kernel(
+    const float *__restrict__ src, Problem pb, SideTab cf, uint8_t *__restrict__ codes, uint8_t *__restrict__ scales) {
+  constexpr int TL = rows128_tl<BS>(), NW = TL / 8;      // waves: 2 c + column half for run c
+  constexpr int GW = 2 * BS / 16;                        // consecutive waves that share a block
+  __shared__ uint32_t red[2][NW];
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int64_t tiles_r = (pb.np + 127) / 128, bt = blockIdx.y;
+  // (the column tile varies fastest: neighbours read adjacent pieces of the same rows of B)
+  const int64_t col = (blockIdx.x % tiles_r) * 128 + 64 * (wave & 1) + lane;
+  const int64_t l = (blockIdx.x / tiles_r) * TL + 16 * (wave >> 1);
+  const Out o = out_of(pb, pb.np, col, l, (l % BS) == 0);
+  // every load unconditional, so that all are in flight together: threads past
+  // an edge read the last column or run again and take no part in the maxima
+  float a[4][16];
+  const float *Bb = src + bt * pb.K * pb.N + (l < pb.kp ? l : pb.kp - 16) * pb.N + (col < pb.np ? col : pb.np - 1);
+#pragma unroll
+  for (int b = 0; b < 4; ++b) {
+    const float *p = Bb + (b >> 1) * pb.kp * pb.N + (b & 1) * pb.np;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) a[b][i] = __builtin_nontemporal_load(p + i * pb.N);
+  }
+  // the T x 4 coefficients, one a lane (T <= 8), so that no term waits on scalar memory
+  const float coef = lane < 4 * (int)pb.T ? cf.dense[lane] : 0.0f;
+  const int64_t code_plane = pb.np * pb.kp, scale_plane = scale_plane_of(pb, pb.np);
+  for (int r = 0; r < (int)pb.T; ++r) {
+    // x = sum_b c_b a_b in ascending b, products and sums rounded separately; -0 + t = t
+    float x[16];
+    bool any = false;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) x[i] = -0.0f;
+#pragma unroll
+    for (int b = 0; b < 4; ++b) {
+      const float c = lane_coef(coef, 4 * r + b);
+      if (c != 0.0f) {
+        any = true;
+#pragma unroll
+        for (int i = 0; i < 16; ++i) x[i] = __fadd_rn(x[i], __fmul_rn(c, a[b][i]));
+      }
+    }
+    if (!any) {
+#pragma unroll
+      for (int i = 0; i < 16; ++i) x[i] = 0.0f;
+    }
+    if (pb.b_bf16) {
+#pragma unroll
+      for (int i = 0; i < 16; ++i) x[i] = bf16_round(x[i]);
+    }
+    float m = fmaxf(fabsf(x[0]), fabsf(x[1]));
+#pragma unroll
+    for (int i = 2; i < 16; ++i) m = fmaxf(m, fabsf(x[i]));
+    uint32_t mb = group_max_bits<32>(o.valid ? __float_as_uint(m) : 0u);
+    mb = max(mb, (uint32_t)__shfl_xor((int)mb, 32, 64));
+    if (lane == 0) red[r & 1][wave] = mb;
+    __syncthreads();
+    const uint32_t *rd = red[r & 1] + (wave & ~(GW - 1));
+    mb = rd[0];
+#pragma unroll
+    for (int k = 1; k < GW; ++k) mb = max(mb, rd[k]);
+    m = __uint_as_float(mb);
+    uint32_t w[4];
+    uint32_t stored;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) w[j] = quantize4<F32>(pb, m, x[4 * j], x[4 * j + 1], x[4 * j + 2], x[4 * j + 3], stored);
+    const int64_t plane = bt * pb.T + r;
+    if (o.valid) *reinterpret_cast<uint4 *>(codes + plane * code_plane + o.code) = make_uint4(w[0], w[1], w[2], w[3]);
+    if (o.leader) store_scale(pb, scales, plane * scale_plane + o.scale, stored);
+  }
 }
 
-// B side with the weight-side deployment granularity (depth 1): the 2-D
-// block maxima (zeroed, then merged by MODE 1) when blocks span 128 rows,
-// then the quantizing pass.
+// B side with the weight-side deployment granularity (depth 1).
 template <int BS, bool F32>
 hipError_t launch_b_deploy(const Problem &pb, const float *src, const SideTab &cf,
-                           uint8_t *codes, uint8_t *scales, uint32_t *amax, hipStream_t st) {
-  if (pb.b_rows > 1) {
-    const int64_t n = pb.batch * pb.T * ((pb.np + 127) / 128) * pb.kblocks;
-    const int64_t blocks = std::min<int64_t>((n + 255) / 256, 4096);
-    hipLaunchKernelGGL(zero_u32_kernel, dim3((unsigned)blocks), dim3(256), 0, st, amax, n);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    e = launch16<1, 1, BS, F32, 1>(pb, src, cf, codes, scales, st, amax);
-    if (e != hipSuccess) return e;
-  }
-  return launch16<1, 1, BS, F32, 2>(pb, src, cf, codes, scales, st, amax);
+                           uint8_t *codes, uint8_t *scales, hipStream_t st) {
+  if (pb.b_rows == 1) return launch16<1, 1, BS, F32, 2>(pb, src, cf, codes, scales, st);
+  constexpr int TL = rows128_tl<BS>();
+  const dim3 grid((unsigned)(((pb.np + 127) / 128) * ((pb.kp + TL - 1) / TL)), (unsigned)pb.batch);
+  hipLaunchKernelGGL((encode_rows128_kernel<BS, F32>), grid, dim3(8 * TL), 0, st, src, pb, cf, codes, scales);
+  return hipGetLastError();
 }
 
 hipError_t launch_b_deploy_any(const Problem &pb, const float *src, const SideTab &cf,
-                               uint8_t *codes, uint8_t *scales, uint32_t *amax, hipStream_t st) {
+                               uint8_t *codes, uint8_t *scales, hipStream_t st) {
   const bool f32 = pb.rule == dev::RULE_FP32_AMAX;
   switch (pb.block) {
-    case 16: return f32 ? launch_b_deploy<16, true>(pb, src, cf, codes, scales, amax, st)
-                        : launch_b_deploy<16, false>(pb, src, cf, codes, scales, amax, st);
-    case 32: return f32 ? launch_b_deploy<32, true>(pb, src, cf, codes, scales, amax, st)
-                        : launch_b_deploy<32, false>(pb, src, cf, codes, scales, amax, st);
-    case 128: return f32 ? launch_b_deploy<128, true>(pb, src, cf, codes, scales, amax, st)
-                         : launch_b_deploy<128, false>(pb, src, cf, codes, scales, amax, st);
+    case 16: return f32 ? launch_b_deploy<16, true>(pb, src, cf, codes, scales, st)
+                        : launch_b_deploy<16, false>(pb, src, cf, codes, scales, st);
+    case 32: return f32 ? launch_b_deploy<32, true>(pb, src, cf, codes, scales, st)
+                        : launch_b_deploy<32, false>(pb, src, cf, codes, scales, st);
+    case 128: return f32 ? launch_b_deploy<128, true>(pb, src, cf, codes, scales, st)
+                         : launch_b_deploy<128, false>(pb, src, cf, codes, scales, st);
   }
   return hipErrorInvalidValue;
 }
@@ -1109,8 +1160,7 @@ int launch_encode(const Problem &pb, const DeviceTables &tab, const float *A, co
   hipError_t e = launch_side<0>(pb, A, a_tab(tab), ws + wl.a_codes, ws + wl.a_scales, st);
   if (e != hipSuccess) return e;
   if (pb.b_rows > 1 || pb.b_bf16)
-    return launch_b_deploy_any(pb, B, b_tab(tab), ws + wl.b_codes, ws + wl.b_scales,
-                               reinterpret_cast<uint32_t *>(ws + wl.b_amax), st);
+    return launch_b_deploy_any(pb, B, b_tab(tab), ws + wl.b_codes, ws + wl.b_scales, st);
   return launch_side<1>(pb, B, b_tab(tab), ws + wl.b_codes, ws + wl.b_scales, st);
 }
 

@@ -180,8 +180,6 @@ int fmm_plan_create(const fmm_real *d, const fmm_plan_desc *desc, fmm_plan **out
   if (q.depth >= 2 && !pb.split) off = align256(off + B * pb.To * 4 * pb.mp * pb.np * sizeof(float));
   wl.products = off;
   if (pb.split) off = align256(off + B * T * pb.mp * pb.np * sizeof(float));
-  wl.b_amax = off;
-  if (pb.b_rows > 1) off = align256(off + B * T * ((pb.np + 127) / 128) * pb.kblocks * sizeof(uint32_t));
   wl.total = off;
 
   // host tables: fp32 flattened U, V (dense rows; and their nonzeros in

@@ -229,3 +229,16 @@ def test_depth3_patterns(name, change, block, rule):
         e = fmm.encode_side(X, T, 3, block, rules[rule], side)
         assert np.array_equal(codes, e["codes"]), side
         assert np.array_equal(scales, e["scales"]), side
+
+
+@pytest.mark.parametrize("case", [
+    # (block, rule, bf16, M, K, N): the 128-row scale blocks' workgroups of 128
+    # columns x 64 (blocks 16, 32) or 128 positions: one position run short of a
+    # tile, one column in the last block, a whole block, several of each
+    (16, 1, False, 34, 160, 2), (16, 0, True, 66, 96, 258), (32, 2, True, 34, 192, 256), (32, 0, False, 256, 448, 254),
+    (128, 1, True, 34, 256, 130), (128, 0, False, 130, 768, 384),
+])
+def test_weight_blocks(case):
+    bs, rule, bf16, M, K, N = case
+    check_case("winograd", "student_t3", 2, M, K, N, 1, bs, rule, seed=38, cfg=2, exact=True, b_rows=128, b_bf16=bf16,
+               ns=False)
