@@ -51,6 +51,7 @@ struct TermArgs {
   float *out;                       // C (depth 1) or partial products (depth >= 2)
   const float *w;                   // R x 4 base decoder weights (zero-padded)
   int64_t mp, np, kp, kblocks, T, To, M, N;
+  int64_t first;                    // this launch's first (product, outer term, tile) item
   int R, depth, tiles_m, tiles_n;
 };
 
@@ -181,7 +182,7 @@ __global__ __launch_bounds__(kThreads, (TA * TB == 1 && MODE != PROMOTE ? 4 : 2)
   int64_t ro, bt;
   {
     const int64_t G = gridDim.x, L = blockIdx.x, x = L & 7;
-    const int64_t id = x * (G >> 3) + min(x, G & 7) + (L >> 3);
+    const int64_t id = g.first + x * (G >> 3) + min(x, G & 7) + (L >> 3);
     const int ntiles = g.tiles_m * g.tiles_n;
     const int64_t item = id / ntiles;
     const int tile = (int)(id - item * ntiles);
@@ -341,10 +342,18 @@ hipError_t launch_edge(const TermArgs &args, int64_t batch, hipStream_t st, int 
   const int64_t t = edge;
   g.tiles_m = (int)((g.mp + t - 1) / t);
   g.tiles_n = (int)((g.np + t - 1) / t);
-  const dim3 grid((unsigned)((int64_t)g.tiles_m * g.tiles_n * g.To * batch));
-  if (edge == 32) hipLaunchKernelGGL((gemm_terms_kernel<LAYOUT, MODE, BS, 1, 1>), grid, dim3(kThreads), 0, st, g);
-  else hipLaunchKernelGGL((gemm_terms_kernel<LAYOUT, MODE, BS, 2, 2>), grid, dim3(kThreads), 0, st, g);
-  return hipGetLastError();
+  // HIP takes fewer than 2^32 threads on a grid axis: more workgroups than that
+  // (8.4 million: tens of GB of small products) go in several launches
+  constexpr int64_t kMaxGrid = (int64_t(1) << 32) / kThreads - 8;
+  const int64_t items = (int64_t)g.tiles_m * g.tiles_n * g.To * batch;
+  for (g.first = 0; g.first < items; g.first += kMaxGrid) {
+    const dim3 grid((unsigned)(items - g.first < kMaxGrid ? items - g.first : kMaxGrid));
+    if (edge == 32) hipLaunchKernelGGL((gemm_terms_kernel<LAYOUT, MODE, BS, 1, 1>), grid, dim3(kThreads), 0, st, g);
+    else hipLaunchKernelGGL((gemm_terms_kernel<LAYOUT, MODE, BS, 2, 2>), grid, dim3(kThreads), 0, st, g);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
 }
 
 }  // namespace
@@ -394,7 +403,7 @@ int launch_products_terms(const Problem &pb, const DeviceTables &tab, const uint
   g.w = tab.w_inner;
   g.mp = pb.mp; g.np = pb.np; g.kp = pb.kp; g.kblocks = pb.kblocks;
   g.T = pb.T; g.To = pb.To; g.M = pb.M; g.N = pb.N;
-  g.R = pb.R; g.depth = pb.depth; g.tiles_m = g.tiles_n = 0;
+  g.R = pb.R; g.depth = pb.depth; g.tiles_m = g.tiles_n = 0; g.first = 0;
   const bool tiled = pb.layout == FMM_LAYOUT_TILE128x128;
 #define FMM_TERMS(L, MODE, BS) return launch_edge<L, MODE, BS>(g, pb.batch, st, edge)
   if (pb.scale_bytes == 4) {

@@ -106,7 +106,7 @@ int fmm_plan_create(const fmm_real *d, const fmm_plan_desc *desc, fmm_plan **out
   const int64_t gm = shaped ? sm : n, gk = shaped ? sk : n, gn = shaped ? sn : n;
   if (q.M % gm || q.K % gk || q.N % gn) return FMM_ERR_SHAPE;
   if ((q.K / gk) % q.block) return FMM_ERR_SHAPE;
-  // grid limits of the launches (batch on grid z/y, terms on grid y)
+  // the launches' grid limit (batch on grid y or z; gemm_terms_kernel, which has it on x, splits its launches)
   if (q.batch > 65535) return FMM_ERR_UNSUPPORTED;
   // the weight-side deployment granularity is built for one level
   if ((q.flags & (FMM_FLAG_B_BLOCK128 | FMM_FLAG_B_BF16)) && q.depth != 1) return FMM_ERR_UNSUPPORTED;

@@ -242,3 +242,23 @@ def test_weight_blocks(case):
     bs, rule, bf16, M, K, N = case
     check_case("winograd", "student_t3", 2, M, K, N, 1, bs, rule, seed=38, cfg=2, exact=True, b_rows=128, b_bf16=bf16,
                ns=False)
+
+
+def test_more_workgroups_than_one_launch_takes():
+    """43691 products of 64 outer terms x three 32-edge tiles are 8388672
+    workgroups of gemm_terms_kernel, whose 2^32 + 2^15 threads are more than
+    one launch's axis holds: products at both ends and in between are those of
+    a plan of one product, bit for bit.  (The last product is the one that two
+    launches share.)"""
+    import torch
+    from paper_2609_26077_amd.runner import FMM
+    batch, M, K, N = 43691, 8, 128, 520
+    g = torch.Generator(device="cuda").manual_seed(12)
+    A = torch.randn((batch, M, K), generator=g, device="cuda")
+    B = torch.randn((batch, K, N), generator=g, device="cuda")
+    C = FMM("cubic8", batch, M, K, N, 3, 16, "pow2_ceil").matmul(A, B)
+    one = FMM("cubic8", 1, M, K, N, 3, 16, "pow2_ceil")
+    for b in (0, batch // 2, batch - 2, batch - 1):
+        assert torch.equal(one.matmul(A[b:b + 1], B[b:b + 1])[0], C[b]), b
+    del A, B, C
+    torch.cuda.empty_cache()
