@@ -964,7 +964,8 @@ hipError_t launch_side(const Problem &pb, const float *src, const SideTab &cf,
     return launch_narrow4<SIDE, true>(pb, src, cf, codes, scales, st);
   }
   switch (pb.depth) {
-    case 1: return launch_wide<SIDE, 1>(pb, src, cf, codes, scales, st);   // (depth 2: launch_pair)
+    case 1: return launch_wide<SIDE, 1>(pb, src, cf, codes, scales, st);
+    case 2: return launch_wide<SIDE, 2>(pb, src, cf, codes, scales, st);
     case 3: return launch_narrow4<SIDE>(pb, src, cf, codes, scales, st);
   }
   return hipErrorInvalidValue;
@@ -1117,29 +1118,55 @@ hipError_t launch_pair_any(const Problem &pb, PairArgs &g, hipStream_t st) {
   return hipErrorInvalidValue;
 }
 
-// One launch for both sides: always at depth 2; at depth 1 while the operands
-// are small enough that the launch saved outweighs A's best workgroup (two
-// waves; us, separate / one launch, block 32: 134 MB 45.9 / 43.1, 157 MB 52.1 /
-// 48.1, 302 MB 87.9 / 91.9, 537 MB 143 / 154; block 128: 33 MB 20.5 / 19.0,
-// 134 MB 59.4 / 61.6).
+// When both sides go in one launch, which saves a launch's latency and fills the
+// chip better where a side has few workgroups, but gives the sides one workgroup
+// size and LDS footprint (us, separate / one launch below).
+// Depth 1: A's best workgroup is two waves with a tile of 16 KB, nine to a CU; in
+// the shared launch, where B's tile sets the LDS, fewer of A's tiles are in
+// flight, so A's tile count decides. Blocks 16 and 32, up to 4608 (A of M x K,
+// its tiles): 3132x4928 (3920) 33.0 / 30.2, 4096x5632 (5630) 37.3 / 39.3, 7180x4672
+// (8530) 57.6 / 64.2, 343 of 1636x64 (35300) 114 / 165; block 128, two of whose
+// workgroups fill a CU, up to 1152: 6226x512 (780) 15.0 / 12.8, 4 of 4348x256 (1090)
+// 20.8 / 15.4, 3090x2304 (1750) 18.8 / 20.9, 7 of 1024x1024 (1790) 17.9 / 20.7, 113
+// of 110x512 (1580) 16.9 / 27.5, 5734x3328 (4670) 31.0 / 38.8. Many bytes gain nothing
+// (whole tiles counted): 302 MB 87.9 / 91.9, 537 MB 143 / 154 (block 32), 134 MB
+// 59.4 / 61.6, 497 of 20x256 by 256x90 (81 MB) 31.0 / 37.9 (block 128).
+// Depth 2, whose sides have one workgroup size by themselves: always (8192^3 286
+// / 274, 1024^3 19.1 / 10.6, 180 of 768^3 393 / 348, 270 of 512x512x1024 429 / 370)
+// but for large batches of products of 1 to 2 MiB (190 of 512^3 186 / 199, 405 372 /
+// 412, 810 of 256x512x256 358 / 387; 71 of 512^3 73 / 63, 324 of 640x512x640 356 /
+// 356, 1621 of 256^3 404 / 370).
 // Other shapes, on the sixteen-wave tiles over up to 16 blocks: always where
 // both sides stage them anyway (more than 8 blocks; <3,3,3;27> 5 MB 14.0 / 8.1,
-// 302 MB 186 / 180).  Grids of up to 8 blocks trade their wider depth-1 tiles
-// for it, whose few workgroups leave a small encode waiting (<2,2,3;11>, block
-// 128, fp32 scales: 3 MB 20.1 / 9.4, 21 MB 23.7 / 17.3, 25 MB 25.4 / 17.0, 42 MB
-// 27.1 / 27.6, 671 MB 313 / 423; block 32: 21 MB 24.4 / 15.6, 42 MB 27.1 / 24.9,
-// 84 MB 49.2 / 46.4, 168 MB 90.1 / 90.6, 671 MB 314 / 403; power-of-two scales
-// alike).
+// 302 MB 186 / 180). Smaller grids trade their wider depth-1 tiles for it:
+// with four blocks and more a side up to 128 MiB, at block 128 32 (<2,2,3;11>
+// block 32: 21 MB 24.4 / 15.6, 105 MB 49.8 / 50.3, 154 MB 63.9 / 69.0; block 128:
+// 21 MB 23.7 / 17.3, 37 MB 24.2 / 21.9, 86 MB 45.1 / 52.1); with fewer, of which a tile
+// holds little, by their tiles of 1024 positions per block, up to 1792, at block 128
+// 1024 (block 32: <3,1,3;9> 1660 tiles 14.6 / 15.0, 2560 18.5 / 21.3, 5250 32.2 / 42.3,
+// <1,2,4;8> 1030 14.2 / 10.5, 6900 37.5 / 54.4; block 128: <3,1,3;9> 1030 13.3 / 9.8,
+// 3000 24.9 / 31.6, <1,2,4;8> 940 14.4 / 13.0, 1160 15.2 / 19.2).
 bool one_launch(const Problem &pb) {
   if (pb.b_rows > 1 || pb.b_bf16 || pb.depth > 2) return false;
-  if (pb.depth == 2) return true;
-  const int64_t bytes = 4 * pb.batch * (pb.M * pb.K + pb.K * pb.N);
+  constexpr int64_t MiB = int64_t(1) << 20;
+  auto up = [](int64_t n, int64_t t) { return (n + t - 1) / t * t; };
+  const int64_t each = 4 * (pb.M * pb.K + pb.K * pb.N), bytes = pb.batch * each;
+  const bool wide = pb.block == 128;
   if (pb.shaped) {
     const int na = pb.gm * pb.gk, nb = pb.gk * pb.gn;
     if (na > 16 || nb > 16) return false;
-    return (na > 8 && nb > 8) || bytes <= (pb.block == 128 ? int64_t(32) << 20 : int64_t(128) << 20);
+    if (na < 4 || nb < 4) return pb.batch * pb.kp * (pb.mp + pb.np) <= (wide ? 1024 : 1792) * 1024;
+    return (na > 8 && nb > 8) || bytes <= (wide ? 32 : 128) * MiB;
   }
-  return bytes <= (pb.block == 128 ? int64_t(64) << 20 : int64_t(192) << 20);
+  if (pb.depth == 2) {
+    // (1024 threads a tile of at least 8 rows x 64 positions, fewer than 2^32 on the axis)
+    if ((up(pb.mp, 8) + up(pb.np, 8)) / 8 * (up(pb.kp, 64) / 64) >= int64_t(1) << 22) return false;
+    return bytes <= 256 * MiB || each < MiB || each > 9 * MiB / 4;
+  }
+  using TA = Tile<1, 16, 0>;
+  const int64_t a = pb.batch * up(pb.mp, TA::TR) * up(pb.kp, TA::TL);       // positions of A's tiles
+  const int64_t b = pb.batch * up(pb.np, kB1Rows) * up(pb.kp, wide ? 128 : 64);
+  return a <= (wide ? 1152 : 4608) * TA::TR * TA::TL && 16 * (a + b) <= (wide ? 64 : 192) * MiB;
 }
 
 }  // namespace

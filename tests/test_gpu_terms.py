@@ -262,3 +262,39 @@ def test_more_workgroups_than_one_launch_takes():
         assert torch.equal(one.matmul(A[b:b + 1], B[b:b + 1])[0], C[b]), b
     del A, B, C
     torch.cuda.empty_cache()
+
+
+@pytest.mark.parametrize("case", [
+    # (depth, block, rule, batch, M, K, N, cubic shape): batches past a bound on the
+    # shared encode launch, whose products alone are within it
+    (2, 32, "pow2_ceil", 140, 512, 512, 512, None),        # 256 MiB of 2 MiB products at depth 2
+    (1, 128, "fp32_amax", 73, 124, 512, 36, None),         # 1152 of A's tiles at block 128 (1168)
+    (1, 32, "pow2_ceil", 700, 100, 64, 18, None),          # 4608 of them at blocks 16 and 32 (4900)
+    (1, 128, "pow2_ocp", 7, 768, 768, 768, (3, 1, 3)),     # 1024 tiles where a side has fewer than four blocks
+    (1, 16, "fp32_amax", 15, 256, 512, 1024, (1, 2, 4)),   # 1792 of them at blocks 16 and 32
+])
+def test_encode_launches(case):
+    """Codes and scales of a batch that takes one encode launch per side are
+    those of its products alone, which take one for both."""
+    import numpy as np
+    import torch
+    import paper_2609_26077_amd as fm
+    from paper_2609_26077_amd.runner import FMM
+    depth, block, rule, batch, M, K, N, shape = case
+    real = "winograd"
+    if shape is not None:
+        m, k, n = shape
+        t = [(i, j, l) for i in range(m) for j in range(k) for l in range(n)]
+        U, V, W = np.zeros((len(t), m * k)), np.zeros((len(t), k * n)), np.zeros((len(t), n * m))
+        for r, (i, j, l) in enumerate(t):
+            U[r, i * k + j] = V[r, j * n + l] = W[r, l * m + i] = 1.0
+        real = fm.fmm_realization_create(U, V, W, shape=shape)
+    g = torch.Generator(device="cuda").manual_seed(13)
+    A = torch.randn((batch, M, K), generator=g, device="cuda")
+    B = torch.randn((batch, K, N), generator=g, device="cuda")
+    whole = FMM(real, batch, M, K, N, depth, block, rule)
+    whole.encode(A, B)
+    alone = FMM(real, 1, M, K, N, depth, block, rule)
+    for b in (0, batch // 2, batch - 1):
+        alone.encode(A[b:b + 1], B[b:b + 1])
+        assert all(torch.equal(x[0], y[b]) for x, y in zip(alone.operands(), whole.operands()))
