@@ -22,7 +22,14 @@
 //   DQ      E8M0 scales, exact-dot flag or block 16: each code converted to
 //           bf16 with its block's power of two, v_mfma_f32_32x32x16_bf16.
 //           The exponents enter one lower on both sides (so that no code
-//           overflows at the largest scale, 2^120) and P_r is multiplied by 4
+//           overflows at the largest scale, 2^120) and P_r is multiplied by 4.
+//           In the tiled layout the instructions accumulate over the whole
+//           contracted axis, as the 128 x 128 kernel's do; in the row layout
+//           each block is summed by itself and added to the fp32 accumulator.
+//           (The matrix core truncates what falls below its accumulator's last
+//           bit at every instruction: over k' = 4096 with rows scaled over four
+//           decades the error against 64 bits is 2.0e-7 of |C| by blocks of
+//           128 and 4.8e-7 in one accumulation, over 256 8.3e-8 either way.)
 //   PROMOTE fp32 scales: codes to bf16 at scale 1, each block's partial sum
 //           times sA sB (formed for the 32 x 32 tile by one
 //           v_mfma_f32_32x32x2_f32: sA in the first contracted position, zero
@@ -73,8 +80,9 @@ __device__ __forceinline__ float e8m0_at(uint32_t w, int i) {
 // One side's operand of one wave: NT row tiles of 32 rows.
 template <int LAYOUT, int MODE, int BS, int NT>
 struct Side {
-  static constexpr bool PIECES = MODE == PROMOTE && BS == 16;   // 8-byte pieces, one block per instruction
-  static constexpr int NSC = MODE == PROMOTE ? kStep / BS : 1;  // scale words a lane holds per step
+  static constexpr bool BLOCKS = MODE == PROMOTE || (MODE == DQ && LAYOUT == FMM_LAYOUT_ROWS);   // each block summed by itself
+  static constexpr bool PIECES = BLOCKS && BS == 16;            // 8-byte pieces, one block per instruction
+  static constexpr int NSC = MODE == PROMOTE ? kStep / BS : PIECES ? 2 : 1;  // scale words a lane holds per step
   const uint8_t *row[NT];      // the lane's row of each tile (its first step)
   const uint8_t *scale[NT];    // its scales
   uint32_t x;                  // the row's chunk swizzle (tiled layout; rows 32 apart share it)
@@ -145,19 +153,23 @@ struct Side {
 #pragma unroll
           for (int b = 0; b < NSC; ++b) f.sc[i][b] = b < nb ? __float_as_uint(s[b]) : 0u;
         } else {
-          // E8M0 bytes in the order of the tiled layout's records (127 = 1 past the end)
+          // E8M0 bytes: MX those of the lane's own instruction halves, DQ by block (127 = 1 past the end)
           const uint8_t *s = scale[i] + kb0;
           auto at = [&](int b) -> uint32_t { return b < nb ? s[b] : 127u; };
           if constexpr (BS == 128) f.sc[i][0] = s[0] * 0x01010101u;
           else if constexpr (MODE == MX) f.sc[i][0] = at(h) | at(2 + h) << 8;
-          else if constexpr (BS == 32) f.sc[i][0] = at(0) | at(2) << 8 | at(1) << 16 | at(3) << 24;
-          else f.sc[i][0] = at(h) | at(2 + h) << 8 | at(4 + h) << 16 | at(6 + h) << 24;
+          else {
+#pragma unroll
+            for (int w = 0; w < NSC; ++w) f.sc[i][w] = at(4 * w) | at(4 * w + 1) << 8 | at(4 * w + 2) << 16 | at(4 * w + 3) << 24;
+          }
         }
       }
     }
     if constexpr (MODE == DQ) {
 #pragma unroll
-      for (int i = 0; i < NT; ++i) f.sc[i][0] -= 0x01010101u;      // bytes are at least 79: no borrow
+      for (int i = 0; i < NT; ++i)
+#pragma unroll
+        for (int w = 0; w < NSC; ++w) f.sc[i][w] -= 0x01010101u;     // bytes are at least 79: no borrow
     }
   }
 
@@ -217,7 +229,7 @@ __global__ __launch_bounds__(kThreads, (TA * TB == 1 && MODE != PROMOTE ? 4 : 2)
         FMM_MX_SUB(0);
         FMM_MX_SUB(1);
 #undef FMM_MX_SUB
-      } else if constexpr (MODE == DQ) {
+      } else if constexpr (!SA::BLOCKS) {
 #pragma unroll
         for (int s = 0; s < 2; ++s)
 #pragma unroll
@@ -242,22 +254,29 @@ __global__ __launch_bounds__(kThreads, (TA * TB == 1 && MODE != PROMOTE ? 4 : 2)
         for (int n = 0; n < 8; ++n) {
           const int s = n >> 2, u = n & 3;
           const int d = SA::PIECES ? 2 * u : 4 * (u >> 1) + 2 * (u & 1);
+          const int blk = n / PER;
+          // (MODE DQ: the block's power of two; the products of a block are then scaled alike)
+          auto scale_of = [&](const uint32_t *sc) { return MODE == PROMOTE ? 1.0f : e8m0_at(sc[blk >> 2], blk & 3); };
           v8bf va[TA], vb[TB];
 #pragma unroll
-          for (int i = 0; i < TA; ++i) va[i] = dequant8(fa.v[s][i][d], fa.v[s][i][d + 1], 1.0f);
+          for (int i = 0; i < TA; ++i) va[i] = dequant8(fa.v[s][i][d], fa.v[s][i][d + 1], scale_of(fa.sc[i]));
 #pragma unroll
-          for (int j = 0; j < TB; ++j) vb[j] = dequant8(fb.v[s][j][d], fb.v[s][j][d + 1], 1.0f);
+          for (int j = 0; j < TB; ++j) vb[j] = dequant8(fb.v[s][j][d], fb.v[s][j][d + 1], scale_of(fb.sc[j]));
 #pragma unroll
           for (int i = 0; i < TA; ++i)
 #pragma unroll
             for (int j = 0; j < TB; ++j)
               part[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(va[i], vb[j], n % PER == 0 ? (v16f){} : part[i][j], 0, 0, 0);
           if (n % PER == PER - 1) {
-            const int blk = n / PER;
 #pragma unroll
             for (int i = 0; i < TA; ++i)
 #pragma unroll
               for (int j = 0; j < TB; ++j) {
+                if constexpr (MODE == DQ) {
+#pragma unroll
+                  for (int e = 0; e < 16; ++e) acc[i][j][e] = __fadd_rn(acc[i][j][e], part[i][j][e]);
+                  continue;
+                }
                 const float x = h == 0 ? __uint_as_float(fa.sc[i][blk]) : 0.0f;
                 const v16f s2 = __builtin_amdgcn_mfma_f32_32x32x2f32(x, __uint_as_float(fb.sc[j][blk]), (v16f){}, 0, 0, 0);
 #pragma unroll
@@ -269,7 +288,7 @@ __global__ __launch_bounds__(kThreads, (TA * TB == 1 && MODE != PROMOTE ? 4 : 2)
     };
 
     const int nk = (int)((g.kp + kStep - 1) / kStep);
-    if constexpr (MODE == PROMOTE && TA * TB > 1) {
+    if constexpr (SA::BLOCKS && TA * TB > 1) {
       // two accumulator sets leave no registers for a second fragment set
       for (int ks = 0; ks < nk; ++ks) {
         typename SA::Frag fa;

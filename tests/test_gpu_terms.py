@@ -298,3 +298,23 @@ def test_encode_launches(case):
     for b in (0, batch // 2, batch - 1):
         alone.encode(A[b:b + 1], B[b:b + 1])
         assert all(torch.equal(x[0], y[b]) for x, y in zip(alone.operands(), whole.operands()))
+
+
+@pytest.mark.parametrize("M,N", [(34, 38), (1538, 1474)])
+@pytest.mark.parametrize("block", [16, 32, 128])
+def test_rows_exact_dot_sums_blocks_apart(block, M, N):
+    """Exact-dot products in the row layout sum each block by itself: beside a
+    first block of 2^12, forty blocks of 2^-11 (the last bit of the sum) made
+    of `block` equal products.  Every partial sum is exact in fp32, so C is;
+    accumulated one matrix instruction after the other, the products below the
+    sum's last bit would be truncated away."""
+    import torch
+    from paper_2609_26077_amd.runner import FMM
+    kp = 41 * block
+    a, b = 2.0 ** -8, 2.0 ** -3 / block
+    A, B = torch.zeros((1, M, 2 * kp)), torch.zeros((1, 2 * kp, N))
+    A[:, :, block:kp], B[:, block:kp] = a, b
+    A[:, :, 0], B[:, 0] = 64.0, 64.0
+    f = FMM("cubic8", 1, M, 2 * kp, N, 1, block, "pow2_ceil", exact_dot=True)
+    C = f.matmul(A.cuda(), B.cuda())
+    assert (C == 2.0 ** 12 + 40 * 2.0 ** -11).all()
