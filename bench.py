@@ -425,7 +425,7 @@ def main():
 
     import torch
     import fmm_inputs as gen
-    from paper_2609_26077_amd import (FMM_LAYOUT_TILE256x64, fmm_operand_views, fmm_realization_metrics,
+    from paper_2609_26077_amd import (FMM_LAYOUT_TILE256x64, fmm_operand_views, fmm_products_kernel, fmm_realization_metrics,
                                       fmm_realization_terms)
     from paper_2609_26077_amd.runner import FMM, error_stats, reference_f64
 
@@ -495,14 +495,7 @@ def main():
     if headline and not args.exact_dot:
         wkey = f"{M}cube_depth{args.depth}_{args.realization}_b{args.block}_{args.rule}_{args.family}"
     counters = recorded_counters(wkey) if wkey else None
-    # the sub-product kernel the plan runs (layout and scale rule decide it)
-    if split:
-        prod_kernel = ("gemm_exact128x128_kernel" if sb == 4 else
-                       "gemm_dq256x128_kernel" if exact else "gemm_tile256x256_kernel")
-    elif a_view.code_layout == 2:
-        prod_kernel = "gemm_tile128_kernel"
-    else:
-        prod_kernel = "gemm_terms_kernel" if exact else "gemm_mx_kernel"
+    prod_kernel, prod_tile = fmm_products_kernel(f.plan).split()
     traffic = None
     step_traffic = None
     if counters:
@@ -543,9 +536,8 @@ def main():
                    "rule": args.rule, "realization": args.realization, "family": args.family,
                    "realization_shape": list(fmm_realization_shape(f.real)[0]),
                    "exact_dot": bool(args.exact_dot),
-                   "subproduct_path": ("large tiles (" + ("256x128" if exact else "256x256") +
-                                       ") + separate W-combine") if split
-                   else "128x128 tiles with the W-combine fused"},
+                   "subproduct_path": f"large tiles ({prod_tile}) + separate W-combine" if split
+                   else f"{prod_tile} tiles with the W-combine fused"},
         "rel_rms_error_vs_fp64": float(np.sqrt(rel_mse)),
         "rel_mse_vs_fp64": rel_mse,
         "kernels_ms": {"encode": enc_ms, "products": prod_ms, "combine": comb_ms},

@@ -323,6 +323,11 @@ int fmm_products(const fmm_plan *p, void *dWs, float *dC, void *stream);
  * fold it into the sub-product kernel at depth 1. */
 int fmm_combine(const fmm_plan *p, void *dWs, float *dC, void *stream);
 
+/* The kernel that fmm_products launches for this plan, with its tile of a
+ * sub-product's rows and columns, e.g. "gemm_tile256x256_kernel 256x256"
+ * (a static string; NULL for a NULL plan). */
+const char *fmm_products_kernel(const fmm_plan *p);
+
 /* fmm_encode followed by fmm_multiply. */
 int fmm_matmul(const fmm_plan *p, const float *dA, const float *dB, float *dC, void *dWs,
                void *stream);

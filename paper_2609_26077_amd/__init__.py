@@ -111,6 +111,7 @@ _SIGS = {
     "fmm_multiply": (ctypes.c_int, [_vp, _vp, _vp, _vp]),
     "fmm_products": (ctypes.c_int, [_vp, _vp, _vp, _vp]),
     "fmm_combine": (ctypes.c_int, [_vp, _vp, _vp, _vp]),
+    "fmm_products_kernel": (ctypes.c_char_p, [_vp]),
     "fmm_matmul": (ctypes.c_int, [_vp, _vp, _vp, _vp, _vp, _vp]),
     "fmm_plan_destroy": (None, [_vp]),
     "fmm_reference_f64": (ctypes.c_int, [_i64, _i64, _i64, _i64, _vp, _vp, _vp, _vp]),
@@ -422,6 +423,10 @@ def fmm_products(p: Plan, ws, C, stream=None) -> None:
 
 def fmm_combine(p: Plan, ws, C, stream=None) -> None:
     _check(_lib.fmm_combine(p.handle, _ptr(ws), _ptr(C), _stream(stream)), "fmm_combine")
+
+
+def fmm_products_kernel(p: Plan) -> str:
+    return _lib.fmm_products_kernel(p.handle).decode()
 
 
 def fmm_matmul(p: Plan, A, B, C, ws, stream=None) -> None:

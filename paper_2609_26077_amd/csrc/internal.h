@@ -180,6 +180,9 @@ int launch_combine(const Problem &pb, const DeviceTables &tab, const uint8_t *ws
 int terms_edge(const Problem &pb);
 int launch_products_terms(const Problem &pb, const DeviceTables &tab, const uint8_t *ws, const Workspace &wl,
                           float *C, int edge, void *stream);
+// the kernel launch_products takes, and its tile ("name rowsxcolumns")
+const char *products_kernel_name(const Problem &pb);
+const char *split_kernel_name(const Problem &pb);   // (large-tile plans)
 int launch_products_split(const Problem &pb, const uint8_t *ws, const Workspace &wl, void *stream);
 int launch_combine_split(const Problem &pb, const DeviceTables &tab, const uint8_t *ws, const Workspace &wl,
                          float *C, void *stream);

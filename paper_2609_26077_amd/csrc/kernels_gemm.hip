@@ -728,6 +728,15 @@ __global__ __launch_bounds__(256) void outer_combine4_kernel(const float *__rest
 
 }  // namespace
 
+const char *products_kernel_name(const Problem &pb) {
+  if (pb.split) return split_kernel_name(pb);
+  switch (terms_edge(pb)) {
+    case 32: return "gemm_terms_kernel 32x32";
+    case 64: return "gemm_terms_kernel 64x64";
+  }
+  return pb.layout == FMM_LAYOUT_TILE128x128 ? "gemm_tile128_kernel 128x128" : "gemm_mx_kernel 128x128";
+}
+
 int launch_products(const Problem &pb, const DeviceTables &tab, const uint8_t *ws,
                     const Workspace &wl, float *C, void *stream) {
   if (pb.batch == 0 || pb.M == 0 || pb.N == 0) return hipSuccess;

@@ -866,6 +866,11 @@ int launch_products_split(const Problem &pb, const uint8_t *ws, const Workspace 
   return hipGetLastError();
 }
 
+const char *split_kernel_name(const Problem &pb) {
+  if (!exact_split(pb)) return "gemm_tile256x256_kernel 256x256";
+  return pb.scale_bytes == 4 ? "gemm_exact128x128_kernel 128x128" : "gemm_dq256x128_kernel 256x128";
+}
+
 int launch_combine_split(const Problem &pb, const DeviceTables &tab, const uint8_t *ws, const Workspace &wl,
                          float *C, void *stream) {
   hipStream_t st = reinterpret_cast<hipStream_t>(stream);

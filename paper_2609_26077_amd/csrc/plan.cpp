@@ -359,6 +359,8 @@ int fmm_products(const fmm_plan *p, void *dWs, float *dC, void *stream) {
                                          dC, stream));
 }
 
+const char *fmm_products_kernel(const fmm_plan *p) { return p ? fmm::products_kernel_name(p->pb) : nullptr; }
+
 int fmm_combine(const fmm_plan *p, void *dWs, float *dC, void *stream) {
   int st = check_multiply(p, dWs, dC);
   if (st != FMM_OK) return st;

@@ -318,3 +318,20 @@ def test_rows_exact_dot_sums_blocks_apart(block, M, N):
     f = FMM("cubic8", 1, M, 2 * kp, N, 1, block, "pow2_ceil", exact_dot=True)
     C = f.matmul(A.cuda(), B.cuda())
     assert (C == 2.0 ** 12 + 40 * 2.0 ** -11).all()
+
+
+@pytest.mark.parametrize("name,case", [
+    # (M, K, N, block, rule, exact, flags)
+    ("gemm_terms_kernel 32x32", (256, 256, 256, 32, "pow2_ceil", False, 0)),
+    ("gemm_terms_kernel 64x64", (1792, 256, 1792, 32, "pow2_ceil", True, 0)),
+    ("gemm_tile128_kernel 128x128", (2304, 768, 2304, 32, "pow2_ceil", False, 0)),
+    ("gemm_mx_kernel 128x128", (3850, 256, 3342, 128, "pow2_ceil", False, 0)),
+    ("gemm_tile256x256_kernel 256x256", (512, 512, 512, 32, "pow2_ceil", False, 8)),
+    ("gemm_dq256x128_kernel 256x128", (512, 512, 512, 16, "pow2_ceil", False, 8)),
+    ("gemm_exact128x128_kernel 128x128", (512, 512, 512, 32, "fp32_amax", False, 0)),
+])
+def test_products_kernel_is_named(name, case):
+    from paper_2609_26077_amd import fmm_products_kernel
+    from paper_2609_26077_amd.runner import FMM
+    M, K, N, block, rule, exact, flags = case
+    assert fmm_products_kernel(FMM("tstar", 1, M, K, N, 1, block, rule, exact_dot=exact, flags=flags).plan) == name
