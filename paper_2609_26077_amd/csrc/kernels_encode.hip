@@ -1131,11 +1131,12 @@ hipError_t launch_pair_any(const Problem &pb, PairArgs &g, hipStream_t st) {
 // of 110x512 (1580) 16.9 / 27.5, 5734x3328 (4670) 31.0 / 38.8. Many bytes gain nothing
 // (whole tiles counted): 302 MB 87.9 / 91.9, 537 MB 143 / 154 (block 32), 134 MB
 // 59.4 / 61.6, 497 of 20x256 by 256x90 (81 MB) 31.0 / 37.9 (block 128).
-// Depth 2, whose sides have one workgroup size by themselves: always (8192^3 286
-// / 274, 1024^3 19.1 / 10.6, 180 of 768^3 393 / 348, 270 of 512x512x1024 429 / 370)
-// but for large batches of products of 1 to 2 MiB (190 of 512^3 186 / 199, 405 372 /
-// 412, 810 of 256x512x256 358 / 387; 71 of 512^3 73 / 63, 324 of 640x512x640 356 /
-// 356, 1621 of 256^3 404 / 370).
+// Depth 2, whose sides have one workgroup size by themselves: to 1 GiB (8192^3 286
+// / 274, 1024^3 19.1 / 10.6, 180 of 768^3 393 / 348, 270 of 512x512x1024 429 / 370;
+// past it 99 of 1024x2048x1024 736 / 804, 220 of 528x2048x300 777 / 813) but for
+// large batches of products of 1 to 2 MiB (190 of 512^3 186 / 199, 405 372 / 412, 810
+// of 256x512x256 358 / 387; 71 of 512^3 73 / 63, 324 of 640x512x640 356 / 356, 1621 of
+// 256^3 404 / 370).
 // Other shapes, on the sixteen-wave tiles over up to 16 blocks: always where
 // both sides stage them anyway (more than 8 blocks; <3,3,3;27> 5 MB 14.0 / 8.1,
 // 302 MB 186 / 180). Smaller grids trade their wider depth-1 tiles for it:
@@ -1143,9 +1144,9 @@ hipError_t launch_pair_any(const Problem &pb, PairArgs &g, hipStream_t st) {
 // block 32: 21 MB 24.4 / 15.6, 105 MB 49.8 / 50.3, 154 MB 63.9 / 69.0; block 128:
 // 21 MB 23.7 / 17.3, 37 MB 24.2 / 21.9, 86 MB 45.1 / 52.1); with fewer, of which a tile
 // holds little, by their tiles of 1024 positions per block, up to 1792, at block 128
-// 1024 (block 32: <3,1,3;9> 1660 tiles 14.6 / 15.0, 2560 18.5 / 21.3, 5250 32.2 / 42.3,
+// 768 (block 32: <3,1,3;9> 1660 tiles 14.6 / 15.0, 2560 18.5 / 21.3, 5250 32.2 / 42.3,
 // <1,2,4;8> 1030 14.2 / 10.5, 6900 37.5 / 54.4; block 128: <3,1,3;9> 1030 13.3 / 9.8,
-// 3000 24.9 / 31.6, <1,2,4;8> 940 14.4 / 13.0, 1160 15.2 / 19.2).
+// 3000 24.9 / 31.6, <1,2,4;8> 770 16.6 / 11.3, 960 14.8 / 19.9, 1160 15.2 / 19.2).
 bool one_launch(const Problem &pb) {
   if (pb.b_rows > 1 || pb.b_bf16 || pb.depth > 2) return false;
   constexpr int64_t MiB = int64_t(1) << 20;
@@ -1155,13 +1156,13 @@ bool one_launch(const Problem &pb) {
   if (pb.shaped) {
     const int na = pb.gm * pb.gk, nb = pb.gk * pb.gn;
     if (na > 16 || nb > 16) return false;
-    if (na < 4 || nb < 4) return pb.batch * pb.kp * (pb.mp + pb.np) <= (wide ? 1024 : 1792) * 1024;
+    if (na < 4 || nb < 4) return pb.batch * pb.kp * (pb.mp + pb.np) <= (wide ? 768 : 1792) * 1024;
     return (na > 8 && nb > 8) || bytes <= (wide ? 32 : 128) * MiB;
   }
   if (pb.depth == 2) {
     // (1024 threads a tile of at least 8 rows x 64 positions, fewer than 2^32 on the axis)
     if ((up(pb.mp, 8) + up(pb.np, 8)) / 8 * (up(pb.kp, 64) / 64) >= int64_t(1) << 22) return false;
-    return bytes <= 256 * MiB || each < MiB || each > 9 * MiB / 4;
+    return bytes <= 256 * MiB || ((each < MiB || each > 9 * MiB / 4) && bytes <= 1024 * MiB);
   }
   using TA = Tile<1, 16, 0>;
   const int64_t a = pb.batch * up(pb.mp, TA::TR) * up(pb.kp, TA::TL);       // positions of A's tiles
