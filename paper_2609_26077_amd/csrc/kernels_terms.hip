@@ -25,7 +25,8 @@
 //           overflows at the largest scale, 2^120) and P_r is multiplied by 4.
 //           In the tiled layout the instructions accumulate over the whole
 //           contracted axis, as the 128 x 128 kernel's do; in the row layout
-//           each block is summed by itself and added to the fp32 accumulator.
+//           each block (at block 16 each two: an instruction spans both) is
+//           summed by itself and added to the fp32 accumulator.
 //           (The matrix core truncates what falls below its accumulator's last
 //           bit at every instruction: over k' = 4096 with rows scaled over four
 //           decades the error against 64 bits is 2.0e-7 of |C| by blocks of
@@ -81,8 +82,8 @@ __device__ __forceinline__ float e8m0_at(uint32_t w, int i) {
 template <int LAYOUT, int MODE, int BS, int NT>
 struct Side {
   static constexpr bool BLOCKS = MODE == PROMOTE || (MODE == DQ && LAYOUT == FMM_LAYOUT_ROWS);   // each block summed by itself
-  static constexpr bool PIECES = BLOCKS && BS == 16;            // 8-byte pieces, one block per instruction
-  static constexpr int NSC = MODE == PROMOTE ? kStep / BS : PIECES ? 2 : 1;  // scale words a lane holds per step
+  static constexpr bool PIECES = MODE == PROMOTE && BS == 16;   // 8-byte pieces, one block per instruction
+  static constexpr int NSC = MODE == PROMOTE ? kStep / BS : 1;  // scale words a lane holds per step
   const uint8_t *row[NT];      // the lane's row of each tile (its first step)
   const uint8_t *scale[NT];    // its scales
   uint32_t x;                  // the row's chunk swizzle (tiled layout; rows 32 apart share it)
@@ -153,23 +154,20 @@ struct Side {
 #pragma unroll
           for (int b = 0; b < NSC; ++b) f.sc[i][b] = b < nb ? __float_as_uint(s[b]) : 0u;
         } else {
-          // E8M0 bytes: MX those of the lane's own instruction halves, DQ by block (127 = 1 past the end)
+          // E8M0 bytes: MX those of the lane's own instruction halves, DQ (block 16: the
+          // lane half's own) in the order of the instructions (127 = 1 past the end)
           const uint8_t *s = scale[i] + kb0;
           auto at = [&](int b) -> uint32_t { return b < nb ? s[b] : 127u; };
           if constexpr (BS == 128) f.sc[i][0] = s[0] * 0x01010101u;
           else if constexpr (MODE == MX) f.sc[i][0] = at(h) | at(2 + h) << 8;
-          else {
-#pragma unroll
-            for (int w = 0; w < NSC; ++w) f.sc[i][w] = at(4 * w) | at(4 * w + 1) << 8 | at(4 * w + 2) << 16 | at(4 * w + 3) << 24;
-          }
+          else if constexpr (BS == 32) f.sc[i][0] = at(0) | at(1) << 8 | at(2) << 16 | at(3) << 24;
+          else f.sc[i][0] = at(h) | at(2 + h) << 8 | at(4 + h) << 16 | at(6 + h) << 24;
         }
       }
     }
     if constexpr (MODE == DQ) {
 #pragma unroll
-      for (int i = 0; i < NT; ++i)
-#pragma unroll
-        for (int w = 0; w < NSC; ++w) f.sc[i][w] -= 0x01010101u;     // bytes are at least 79: no borrow
+      for (int i = 0; i < NT; ++i) f.sc[i][0] -= 0x01010101u;      // bytes are at least 79: no borrow
     }
   }
 
@@ -248,15 +246,14 @@ __global__ __launch_bounds__(kThreads, (TA * TB == 1 && MODE != PROMOTE ? 4 : 2)
                 acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(va[i], vb[j], acc[i][j], 0, 0, 0);
           }
       } else {
-        constexpr int PER = BS / 16;                          // instructions per block
+        constexpr int PER = MODE == DQ && BS == 16 ? 2 : BS / 16;   // instructions per sum
         v16f part[TA][TB];
 #pragma unroll
         for (int n = 0; n < 8; ++n) {
           const int s = n >> 2, u = n & 3;
           const int d = SA::PIECES ? 2 * u : 4 * (u >> 1) + 2 * (u & 1);
           const int blk = n / PER;
-          // (MODE DQ: the block's power of two; the products of a block are then scaled alike)
-          auto scale_of = [&](const uint32_t *sc) { return MODE == PROMOTE ? 1.0f : e8m0_at(sc[blk >> 2], blk & 3); };
+          auto scale_of = [&](const uint32_t *sc) { return MODE == PROMOTE ? 1.0f : e8m0_at(sc[0], blk); };
           v8bf va[TA], vb[TB];
 #pragma unroll
           for (int i = 0; i < TA; ++i) va[i] = dequant8(fa.v[s][i][d], fa.v[s][i][d + 1], scale_of(fa.sc[i]));

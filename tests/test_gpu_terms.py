@@ -303,17 +303,18 @@ def test_encode_launches(case):
 @pytest.mark.parametrize("M,N", [(34, 38), (1538, 1474)])
 @pytest.mark.parametrize("block", [16, 32, 128])
 def test_rows_exact_dot_sums_blocks_apart(block, M, N):
-    """Exact-dot products in the row layout sum each block by itself: beside a
-    first block of 2^12, forty blocks of 2^-11 (the last bit of the sum) made
-    of `block` equal products.  Every partial sum is exact in fp32, so C is;
-    accumulated one matrix instruction after the other, the products below the
-    sum's last bit would be truncated away."""
+    """Exact-dot products in the row layout sum each block (at block 16 each
+    two) by itself: beside a first sum of 2^12, forty sums of 2^-11 (the last
+    bit of the whole) made of equal products.  Every partial sum is exact in
+    fp32, so C is; accumulated one matrix instruction after the other, the
+    products below the sum's last bit would be truncated away."""
     import torch
     from paper_2609_26077_amd.runner import FMM
-    kp = 41 * block
-    a, b = 2.0 ** -8, 2.0 ** -3 / block
+    span = max(block, 32)
+    kp = 41 * span
+    a, b = 2.0 ** -8, 2.0 ** -3 / span
     A, B = torch.zeros((1, M, 2 * kp)), torch.zeros((1, 2 * kp, N))
-    A[:, :, block:kp], B[:, block:kp] = a, b
+    A[:, :, span:kp], B[:, span:kp] = a, b
     A[:, :, 0], B[:, 0] = 64.0, 64.0
     f = FMM("cubic8", 1, M, 2 * kp, N, 1, block, "pow2_ceil", exact_dot=True)
     C = f.matmul(A.cuda(), B.cuda())
