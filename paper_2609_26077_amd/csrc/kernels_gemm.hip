@@ -49,6 +49,18 @@ typedef float v16f __attribute__((ext_vector_type(16)));
 typedef __bf16 v8bf __attribute__((ext_vector_type(8)));
 typedef __bf16 v2bf __attribute__((ext_vector_type(2)));
 
+// eight e4m3 codes (little-endian in two words) -> eight bf16, exactly
+__device__ __forceinline__ v8bf codes_bf16(uint2 w) {
+  const v2bf a = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8((int)w.x, 1.0f, false);
+  const v2bf b = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8((int)w.x, 1.0f, true);
+  const v2bf c = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8((int)w.y, 1.0f, false);
+  const v2bf d = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8((int)w.y, 1.0f, true);
+  v8bf r;
+  r[0] = a[0]; r[1] = a[1]; r[2] = b[0]; r[3] = b[1];
+  r[4] = c[0]; r[5] = c[1]; r[6] = d[0]; r[7] = d[1];
+  return r;
+}
+
 constexpr int BM = 128, BN = 128, BK = 128;
 constexpr int kThreads = 256;
 
@@ -642,6 +654,136 @@ __global__ __launch_bounds__(kTileThreads, 1) void gemm_tile128_kernel(GemmArgs 
 }
 
 // ---------------------------------------------------------------------------
+// Row layout at block 128, exact-dot or fp32 scales, on 128 x 128 tiles: a
+// 128-byte K step is one block, whose products are summed on the bf16 matrix
+// cores with the codes at scale 1 and promoted by sA[row] * sB[col] in fp32.
+// ---------------------------------------------------------------------------
+template <bool F32>
+__global__ __launch_bounds__(kThreads, 1) void gemm_promote_kernel(GemmArgs g) {
+  __shared__ uint4 lds_raw[2 * 2 * BM * BK / 16];
+  __shared__ float lsa[BM], lsb[BN];
+  uint8_t *lds = reinterpret_cast<uint8_t *>(lds_raw);
+  const int t = threadIdx.x;
+  const int wave = t >> 6, lane = t & 63;
+  const int wm = wave >> 1, wn = wave & 1;
+  const int r32 = lane & 31, h = lane >> 5;
+  const int64_t tm = blockIdx.x / g.tiles_n, tn = blockIdx.x % g.tiles_n;
+  const int64_t ro = blockIdx.y, bt = blockIdx.z;
+  const int64_t pm0 = tm * BM, pn0 = tn * BN;
+  const int64_t rowa0 = pm0 + wm * 64, rowb0 = pn0 + wn * 64;
+  const int64_t nsteps = g.kp / BK;
+  const int64_t total = (int64_t)g.R * nsteps;
+
+  v16f acc[2][2], quad[4][2][2];
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+      acc[i][j] = (v16f){};
+#pragma unroll
+      for (int q = 0; q < 4; ++q) quad[q][i][j] = (v16f){};
+    }
+
+  Stage st;
+  if (total > 0) {
+    load_stage(g, bt, ro * g.R, 0, pm0, pn0, st);
+    store_stage(lds, lds + BM * BK, st);
+  }
+
+  for (int64_t it = 0; it < total; ++it) {
+    const int ri = (int)(it / nsteps);
+    const int64_t ks = it % nsteps;
+    const int64_t r = ro * g.R + ri;
+    const int buf = (int)(it & 1);
+    const bool more = it + 1 < total;
+    // the step's scales into LDS (fp32 values), one a thread
+    {
+      const bool isb = t >= BM;
+      const int row = t & (BM - 1);
+      const int64_t p = (isb ? pn0 : pm0) + row, rows = isb ? g.np : g.mp;
+      float v = 0.f;
+      if (p < rows) {
+        const int64_t idx = ((bt * g.T + r) * rows + p) * g.kblocks + ks;
+        const uint8_t *base = isb ? g.sb : g.sa;
+        if constexpr (F32) v = reinterpret_cast<const float *>(base)[idx];
+        else v = __uint_as_float((uint32_t)base[idx] << 23);   // 2^(e8m0 - 127)
+      }
+      (isb ? lsb : lsa)[row] = v;
+    }
+    __syncthreads();
+    if (more) {
+      const int64_t rn = ro * g.R + (it + 1) / nsteps;
+      const int64_t kn = ((it + 1) % nsteps) * BK;
+      load_stage(g, bt, rn, kn, pm0, pn0, st);
+    }
+    const uint8_t *la = lds + buf * 2 * BM * BK;
+    const uint8_t *lb = la + BM * BK;
+    v16f tmp[2][2];
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+      for (int j = 0; j < 2; ++j) tmp[i][j] = (v16f){};
+    for (int c = 0; c < BK / 16; ++c) {   // 16-byte chunk within the step
+      v8bf fa[2], fb[2];
+#pragma unroll
+      for (int i = 0; i < 2; ++i) {
+        const int rowa = wm * 64 + 32 * i + r32, rowb = wn * 64 + 32 * i + r32;
+        fa[i] = codes_bf16(*reinterpret_cast<const uint2 *>(la + swz(rowa, c) + 8 * h));
+        fb[i] = codes_bf16(*reinterpret_cast<const uint2 *>(lb + swz(rowb, c) + 8 * h));
+      }
+#pragma unroll
+      for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+          tmp[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[i], fb[j], tmp[i][j], 0, 0, 0);
+    }
+    // promote: acc += sA[row] sB[col] tmp
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+      for (int j = 0; j < 2; ++j) {
+        const float sbv = lsb[wn * 64 + 32 * j + r32];
+#pragma unroll
+        for (int e = 0; e < 16; ++e) {
+          const int row = wm * 64 + 32 * i + 8 * (e >> 2) + 4 * h + (e & 3);
+          acc[i][j][e] = __fmaf_rn(lsa[row] * sbv, tmp[i][j][e], acc[i][j][e]);
+        }
+      }
+    if (ks == nsteps - 1) {
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const float wq = g.w[4 * ri + q];
+        if (wq != 0.0f) {
+#pragma unroll
+          for (int i = 0; i < 2; ++i)
+#pragma unroll
+            for (int j = 0; j < 2; ++j)
+#pragma unroll
+              for (int e = 0; e < 16; ++e) quad[q][i][j][e] = __fmaf_rn(wq, acc[i][j][e], quad[q][i][j][e]);
+        }
+      }
+#pragma unroll
+      for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j) acc[i][j] = (v16f){};
+    }
+    __syncthreads();   // every wave is done with this buffer and with the scales
+    if (more) {
+      uint8_t *na = lds + (buf ^ 1) * 2 * BM * BK;
+      store_stage(na, na + BM * BK, st);
+    }
+  }
+
+#pragma unroll
+  for (int q = 0; q < 4; ++q)
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+      for (int j = 0; j < 2; ++j)
+        store_tile(g, bt, ro, q, rowa0 + 32 * i, rowb0 + 32 * j, quad[q][i][j]);
+}
+
+// ---------------------------------------------------------------------------
 // Outer combine (depth >= 2): C block (I, K) with I = 2 I_o + i, K = 2 K_o + k:
 //   C = sum_{r_o} w_outer[r_o][K_o 2^(l-1) + I_o] * Q[r_o][2k + i]
 // ---------------------------------------------------------------------------
@@ -734,7 +876,8 @@ const char *products_kernel_name(const Problem &pb) {
     case 32: return "gemm_terms_kernel 32x32";
     case 64: return "gemm_terms_kernel 64x64";
   }
-  return pb.layout == FMM_LAYOUT_TILE128x128 ? "gemm_tile128_kernel 128x128" : "gemm_mx_kernel 128x128";
+  if (pb.layout == FMM_LAYOUT_TILE128x128) return "gemm_tile128_kernel 128x128";
+  return pb.scale_bytes == 4 || pb.exact_dot ? "gemm_promote_kernel 128x128" : "gemm_mx_kernel 128x128";
 }
 
 int launch_products(const Problem &pb, const DeviceTables &tab, const uint8_t *ws,
@@ -778,6 +921,10 @@ int launch_products(const Problem &pb, const DeviceTables &tab, const uint8_t *w
     else
       FMM_TILE128(128, false);
 #undef FMM_TILE128
+  } else if (pb.scale_bytes == 4) {
+    hipLaunchKernelGGL(gemm_promote_kernel<true>, grid, dim3(kThreads), 0, st, g);
+  } else if (pb.exact_dot) {
+    hipLaunchKernelGGL(gemm_promote_kernel<false>, grid, dim3(kThreads), 0, st, g);
   } else {
     hipLaunchKernelGGL(gemm_mx_kernel, grid, dim3(kThreads), 0, st, g);   // (fp8, row layout)
   }

@@ -37,6 +37,8 @@
 //           in the second) into the fp32 accumulator
 #include <hip/hip_runtime.h>
 
+#include <cmath>
+
 #include "device.h"
 #include "internal.h"
 
@@ -372,8 +374,6 @@ hipError_t launch_edge(const TermArgs &args, int64_t batch, hipStream_t st, int 
   return hipSuccess;
 }
 
-}  // namespace
-
 // Which products take this kernel, by the number of workgroups n32 and n64
 // (tiles of 32 or 64 rows and columns, times outer terms, times products) and
 // n128 of the 128 x 128 tiles.
@@ -389,24 +389,66 @@ hipError_t launch_edge(const TermArgs &args, int64_t batch, hipStream_t st, int 
 // 32-edge tiles from n32 = 768 on (2048x1024x2048: 18.9 / 20.5, 2048^3 one
 // more step in k': 26 / 33), and only the first round is worth it.
 //
-// Row layout: exact-dot plans always; fp8 plans unless the 128 x 128 tiles
-// fill their rounds of the chip (4000x4096x4000, 256 tiles: 328 against
-// gemm_mx_kernel's 298; 3000^3, 144 tiles: 165 / 228; 2000x1472x2000: 28 /
-// 125; 500x512x500: 8 / 54).  64-edge tiles from 560 32-edge tiles per
-// round on (us, 32 / 64: n32 = 484 27.7 / 32.8, 605 60 / 47, 968 50 / 34; 1008 in two rounds 39 / 52;
-// 2209 in three 216 / 165).
+// Row layout, fp32 scales at blocks 16 and 32: 64-edge tiles from 560 32-edge tiles
+// per round of them on (k' 2048 2000x2000: 828 / 453; k' 128 127x127, 2800 of them:
+// 1036 / 754; k' 8192 100x2000: 200 / 411).
+//
+// Row layout otherwise: the least of three fitted times, of this kernel on either
+// tile and of the 128 x 128 kernels, gemm_mx_kernel and at block 128
+// gemm_promote_kernel (at blocks 16 and 32 its like lost to this kernel at every
+// size measured). Rounds r32, r64 and r128 are the workgroups over the CUs; several
+// 32-edge workgroups share a CU and start as others end, 64-edge ones hold a CU each
+// (their time goes by whole rounds and, with L2 shared, by the tiles), a round of
+// 128 x 128 tiles walks its R terms in turn:
+//   t32 = r32 (a + b nk)    t64 = r64 (c + d nk) + ceil(r64) (e + f nk)
+//   t128 = R ceil(r128) (g + h nk)         us, nk = k' / 128 rounded up
+// The per-term kernel's lanes read rows k' apart straight from L2: at k' a multiple
+// of 256 or 1024 their codes and short rows of scales (blocks 16 and 32) meet on few
+// of its channels, 1.3 and 1.65 times on 32-edge tiles, 1.15 and 1.3 on 64-edge ones;
+// block 128 shows 1.15 from k' 3072 on.
+// Fitted to 3400 plans of k' 32 .. 2200, 40 .. 6000 tiles of 128 and depths 1 to 3,
+// then t32 raised by 4% and t128 by 2 to 4% (the costlier mistakes); on another 1000
+// the choice is on average 1% off the best. Measured, us, 32 / 64 / 128 edge (k', m' x
+// n', r128):
+//   fp8, block 32   96 387x579 9.8 351 / 420 / 383; 160 203x503 1.5 68 / 91 / 105;
+//                   928 263x559 8.6 1192 / 905 / 1400; 2048 2000x2000 1.0 592 / 331 / 300
+//   fp8, block 128  128 1144x1576 3.2 167 / 165 / 143; 256 2439x52 0.9 40 / 36 / 56;
+//                   2048 2000x2000 1.0 446 / 259 / 295
+//   exact-dot, 128  128 112x226 11.3 685 / 633 / 521; 128 35x610 1.1 33 / 36 / 72;
+//                   256 106x86 20.5 1307 / 1513 / 1312; 2048 2000x2000 1.0 449 / 271 / 324
+//   fp32 scales, 128  128 128x128 10.5 855 / 641 / 462; 128 1326x123 0.95 69 / 53 / 45;
+//                   256 512x768 4.6 488 / 342 / 304; 2048 2000x2000 1.0 534 / 296 / 328
+struct EdgeTimes {
+  double a, b, c, d, e, f, g, h;    // g = 0: no 128 x 128 kernel
+};
+EdgeTimes edge_times(const Problem &pb) {
+  const bool wide = pb.block == 128;
+  if (pb.scale_bytes == 4) return {2.75, 2.1, 1.75, 1.9, 7.0, 2.5, 2.75, 2.75};
+  if (pb.exact_dot && wide) return {2.05, 1.83, 2.15, 1.0, 6.9, 2.9, 2.65, 2.65};
+  if (pb.exact_dot || pb.block == 16) return {1.1, 2.15, 1.1, 2.6, 5.2, 3.5, 0, 0};
+  if (wide) return {1.85, 1.8, 0.95, 2.1, 7.6, 1.65, 2.25, 2.4};
+  return {1.25, 1.5, 1.5, 1.65, 5.3, 2.15, 2.05, 2.5};
+}
+
+}  // namespace
+
 int terms_edge(const Problem &pb) {
   auto count = [&](int64_t e) { return ((pb.mp + e - 1) / e) * ((pb.np + e - 1) / e) * pb.To * pb.batch; };
   const int64_t n32 = count(32), n64 = count(64), n128 = count(128), ncu = pb.ncu;
-  const int64_t rounds = (n64 + ncu - 1) / ncu;
   if (pb.layout == FMM_LAYOUT_TILE128x128) {
     if (16 * n128 > 5 * ncu) return 0;
-    return n32 > 3 * ncu && rounds == 1 ? 64 : 32;
+    return n32 > 3 * ncu && n64 <= ncu ? 64 : 32;
   }
-  const bool mx = pb.scale_bytes == 1 && !pb.exact_dot && pb.block != 16;
-  const int64_t rounds128 = (n128 + ncu - 1) / ncu;
-  if (mx && 8 * n128 >= 7 * rounds128 * ncu) return 0;
-  return 16 * n32 > 35 * ncu * rounds ? 64 : 32;
+  const double r32 = (double)n32 / ncu, r64 = (double)n64 / ncu;
+  if (pb.scale_bytes == 4 && pb.block != 128) return r32 > 35.0 / 16 * std::ceil(r64) ? 64 : 32;
+  const EdgeTimes t = edge_times(pb);
+  const double nk = (double)((pb.kp + kStep - 1) / kStep);
+  const bool far = pb.block == 128 && pb.kp >= 3072, even = pb.block < 128 && pb.kp % 256 == 0, most = even && pb.kp % 1024 == 0;
+  const double t32 = (most ? 1.65 : even ? 1.3 : far ? 1.15 : 1.0) * r32 * (t.a + t.b * nk);
+  const double t64 = (most ? 1.3 : even || far ? 1.15 : 1.0) * (r64 * (t.c + t.d * nk) + std::ceil(r64) * (t.e + t.f * nk));
+  const double t128 = pb.R * std::ceil((double)n128 / ncu) * (t.g + t.h * nk);
+  if (t.g > 0 && t128 < t32 && t128 < t64) return 0;
+  return t64 < t32 ? 64 : 32;
 }
 
 int launch_products_terms(const Problem &pb, const DeviceTables &tab, const uint8_t *ws, const Workspace &wl,

@@ -336,3 +336,27 @@ def test_products_kernel_is_named(name, case):
     from paper_2609_26077_amd.runner import FMM
     M, K, N, block, rule, exact, flags = case
     assert fmm_products_kernel(FMM("tstar", 1, M, K, N, 1, block, rule, exact_dot=exact, flags=flags).plan) == name
+
+
+EDGE64, TILE128 = "gemm_terms_kernel 64x64", "gemm_%s_kernel 128x128"
+
+
+@pytest.mark.parametrize("bs,rule,exact,case", [
+    # 256 tiles of 64 x 64, the last ones one row and one column wide, K one block past a step
+    (bs, rule, exact, (EDGE64, 1, 1, 1922, 2 * (128 + bs), 1922))
+    for bs, rule, exact in [(16, 0, False), (32, 0, False), (128, 0, False), (16, 1, False), (32, 1, False), (32, 1, True),
+                            (128, 1, False), (128, 1, True)]] + [
+    # tiles of 128 x 128 that fill seven eighths of the chip, one step and three; at depth 2 one
+    # tile a product, over outer terms and products
+    (128, rule, exact, (TILE128 % kernel, *sizes))
+    for rule, exact, kernel in [(1, False, "mx"), (1, True, "promote"), (0, False, "promote")]
+    for sizes in [(1, 1, 3850, 256, 3342), (1, 1, 3850, 768, 3342), (2, 36, 500, 512, 496)]])
+def test_row_layout_dispatch(bs, rule, exact, case):
+    """Which kernel a row-layout plan's products take, and its results."""
+    from paper_2609_26077_amd import fmm_products_kernel
+    from paper_2609_26077_amd.runner import FMM
+    kernel, depth, batch, M, K, N = case
+    f = FMM("strassen", batch, M, K, N, depth, bs, rule, exact_dot=exact)
+    assert fmm_products_kernel(f.plan) == kernel
+    check_case("strassen", "gaussian", batch, M, K, N, depth, bs, rule, seed=39, cfg=2, exact=exact, layout=ROWS,
+               check_every=35 if batch > 1 else None)
