@@ -28,26 +28,45 @@ bool is_gfx950(int dev) {
   return std::strncmp(prop.gcnArchName, "gfx950", 6) == 0;
 }
 
+// The compute units of the current device (256, gfx950's, if there is none:
+// the layout is chosen before the device is checked).
+int compute_units() {
+  int dev = 0, ncu = 0;
+  if (hipGetDevice(&dev) != hipSuccess ||
+      hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || ncu <= 0)
+    return 256;
+  return ncu;
+}
+
 // Whether the fused 128 x 128 kernel beats the large tiles and their W-combine
 // pass on a depth-1 product with E8M0 scales and k' >= 1024: it writes no P_r,
-// but a round of one tile per CU costs the same however many CUs it fills,
+// but a round of one tile per CU costs much the same however many CUs it fills,
 // and its smaller tiles need twice the L2 bytes per flop, so it wins where the
-// tiles fill their rounds and k' is not large.  Times in us, fitted to
-// measurement (fused / large tiles + combine, T*, block 32; fp8, then
-// exact-dot): 4096x2048x4096 53 / 78 and 71 / 91; 8192x2048x8192 213 / 261 and
-// 290 / 329; 16 of 2048^3 206 / 262 and 287 / 331; 4096^3 89 / 99 and 132 /
-// 139; and the other way round 3072x2048x3072 48 / 46, 65 / 53; 6144x4096x6144
-// 243 / 201, 356 / 287; 4096x8192x4096 160 / 144, 253 / 238; 8192^3 634 /
-// 530, 987 / 854.
-bool fused_beats_large_tiles(int64_t batch, int64_t R, int64_t mp, int64_t kp, int64_t np, bool exact) {
-  constexpr double kCUs = 256;
+// tiles fill their rounds and k' is not large.  Times in us, fitted to 870 plans
+// of both paths with more than 80 tiles of 128 (4% standard deviation; an exact-dot
+// round of large tiles is two 256 x 128 tiles per CU, and half a round half its
+// time); taken only where it is 2% (exact-dot 3.5%) the faster: of 433 other plans it
+// was taken for 103, once where it is over 3% slower (4.7%).  Fused / large tiles +
+// combine, T*, block 32, fp8: 4096x2048x4096 58 / 80, 8192x2048x8192 229 / 289, 16 of
+// 2048^3 213 / 293, 4096^3 89 / 99; 3072x2048x3072 48 / 45, 6144x4096x6144 246 / 198,
+// 4096x8192x4096 159 / 140, 8192^3 641 / 521; exact-dot: 4096x2048x4096 73 / 91, 16 of
+// 2048^3 285 / 358, 4096^3 129 / 137; 3072x4096x4096 117 / 107, 11 of 5632x6144x512 406 /
+// 363, 6144x4096x6144 364 / 274, 8192^3 980 / 845.
+bool fused_beats_large_tiles(int64_t batch, int64_t R, int64_t mp, int64_t kp, int64_t np, bool exact, int ncu) {
   const double outputs = (double)batch * mp * np, k = (double)kp;
-  const double fused_rounds = std::ceil(outputs / (128 * 128) / kCUs);
-  const double fused = R * fused_rounds * (exact ? 1.5 + 1.09 * k / 128 : 2.1 + 0.66 * k / 128);
-  const double large_rounds = std::ceil(R * outputs / (256 * 256) / kCUs);   // (exact-dot: two 256 x 128 tiles per CU)
-  const double large = large_rounds * (exact ? 16 + 22.5 * k / 1024 : 9 + 12.5 * k / 1024) +
-                       4 * (R + 4) * outputs / 6.4e6;                        // the combine's bytes at 6.4 TB/s
-  return fused < large;
+  const double tiles = outputs / (128 * 128) / ncu, large_tiles = R * outputs / (256 * 256) / ncu;   // in rounds
+  const double combine = 4 * (R + 4) * outputs / 6.4e6;                                              // its bytes at 6.4 TB/s
+  const double fr = std::ceil(tiles);
+  if (exact) {
+    const double lr = std::ceil(2 * large_tiles) / 2;
+    const double fused = R * (fr * 1.5 + (0.773 * fr + 0.308 * tiles) * k / 128) + 2;
+    const double large = -7.1 * lr + (21.9 * lr + 2.44 * large_tiles) * k / 1024 + 1.94 * combine + 4.4;
+    return fused < 0.965 * large;
+  }
+  const double lr = std::ceil(large_tiles);
+  const double fused = R * (fr * 1.6 + (0.487 * fr + 0.205 * tiles) * k / 128) + 2.5;
+  const double large = -1.3 * lr + (10.6 * lr + 1.62 * large_tiles) * k / 1024 + 1.81 * combine + 4.8;
+  return fused < 0.98 * large;
 }
 
 }  // namespace
@@ -149,7 +168,7 @@ int fmm_plan_create(const fmm_real *d, const fmm_plan_desc *desc, fmm_plan **out
   pb.scale_bytes = q.rule == FMM_RULE_FP32_AMAX ? 4 : 1;
   pb.exact_dot = (q.flags & FMM_FLAG_EXACT_DOT) ? 1 : 0;
   pb.b_rows = (q.flags & FMM_FLAG_B_BLOCK128) ? 128 : 1;
-  pb.ncu = 256;   // (replaced by the device's own count below)
+  pb.ncu = compute_units();
   pb.b_bf16 = (q.flags & FMM_FLAG_B_BF16) ? 1 : 0;
   // E8M0 scales have a fused 128 x 128 kernel: at blocks 32 and 128 on either
   // path (the fp8 matrix cores, or the exact-dot flag's folded-scale form),
@@ -158,7 +177,7 @@ int fmm_plan_create(const fmm_real *d, const fmm_plan_desc *desc, fmm_plan **out
   const bool fused_exists = pb.scale_bytes == 1 && (q.block == 16 || q.block == 32 || q.block == 128);
   const bool exact = pb.exact_dot || q.block == 16;
   const bool fused_fills = q.depth == 1 && pb.kp % 128 == 0 &&
-                           fused_beats_large_tiles(q.batch, T, mp, kp, np, exact);
+                           fused_beats_large_tiles(q.batch, T, mp, kp, np, exact, pb.ncu);
   pb.split = shaped || (split_shape && (!fused_exists || (q.flags & FMM_FLAG_LARGE_TILE) ||
                                         (pb.kp >= fmm::kSplitMinK && !fused_fills)));
   // fused 128 x 128 path: E8M0 scales at blocks 32 and 128 (the fp8 matrix
@@ -273,8 +292,6 @@ int fmm_plan_create(const fmm_real *d, const fmm_plan_desc *desc, fmm_plan **out
     return FMM_ERR_DEVICE;
   }
   p->device = dev;
-  int ncu = 0;
-  if (hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess && ncu > 0) pb.ncu = ncu;
   void *dt = nullptr;
   int e = hipMalloc(&dt, tot);
   if (e == hipSuccess) e = hipMemcpy(dt, host.data(), tot, hipMemcpyHostToDevice);

@@ -360,3 +360,16 @@ def test_row_layout_dispatch(bs, rule, exact, case):
     assert fmm_products_kernel(f.plan) == kernel
     check_case("strassen", "gaussian", batch, M, K, N, depth, bs, rule, seed=39, cfg=2, exact=exact, layout=ROWS,
                check_every=35 if batch > 1 else None)
+
+
+@pytest.mark.parametrize("case", [
+    (11, 5632, 6144, 512, 16), (1, 3072, 4096, 4096, 16), (1, 5120, 2304, 4608, 32), (1, 7168, 5120, 1536, 128),
+])
+def test_exact_dot_takes_the_large_tiles(case):
+    """Exact-dot products at depth 1 and k' >= 1024 on which the fused kernel was
+    measured 15 to 26% slower than the large tiles and their W-combine pass."""
+    from paper_2609_26077_amd import fmm_products_kernel
+    from paper_2609_26077_amd.runner import FMM
+    batch, M, K, N, block = case
+    f = FMM("tstar", batch, M, K, N, 1, block, "pow2_ceil", exact_dot=True)
+    assert fmm_products_kernel(f.plan) == "gemm_dq256x128_kernel 256x128"
