@@ -792,11 +792,13 @@ hipError_t launch16(const Problem &pb, const float *src, const SideTab &cf,
 // row segment.  Per term every wave reduces the maximum of its 64 columns x 16
 // positions, the workgroup's waves meet at one barrier (the maxima's slots
 // alternate by term, so no second one is needed), and each thread quantizes its
-// run.  HBM bounds it, and at block 128 the one workgroup a CU holds, which loads
+// run.  Where the tiles leave CUs idle, several workgroups share a tile's terms
+// (298x256x1102 19.8 us in the two passes below, 20.9 in one workgroup a tile, 10.3
+// now; 2048^3 32.0, 27.5, 19.3).  HBM bounds it, and at block 128 the one workgroup a CU holds, which loads
 // and computes in turn.  Two passes over B, the first for the maxima alone, and
 // a pass clearing these took (encode of both sides, us, before / now): 8192^3
 // fp32 scales at block 128 230 / 196, power-of-two scales at block 128 224 / 165, at
-// block 32 223 / 147; 4096^3 block 128 69.5 / 49.7; 512^3 block 128 23.1 / 22.9.
+// block 32 223 / 147; 4096^3 block 128 69.5 / 49.7; 512^3 block 128 23.9 / 12.0.
 // ---------------------------------------------------------------------------
 template <int BS>
 constexpr int rows128_tl() { return BS == 128 ? 128 : 64; }
@@ -827,7 +829,8 @@ __global__ __launch_bounds__(8 * rows128_tl<BS>(), 4) void encode_rows128_kernel
   // the T x 4 coefficients, one a lane (T <= 8), so that no term waits on scalar memory
   const float coef = lane < 4 * (int)pb.T ? cf.dense[lane] : 0.0f;
   const int64_t code_plane = pb.np * pb.kp, scale_plane = scale_plane_of(pb, pb.np);
-  for (int r = 0; r < (int)pb.T; ++r) {
+  int slot = 0;
+  for (int r = blockIdx.z; r < (int)pb.T; r += gridDim.z, slot ^= 1) {
     // x = sum_b c_b a_b in ascending b, products and sums rounded separately; -0 + t = t
     float x[16];
     bool any = false;
@@ -855,9 +858,9 @@ __global__ __launch_bounds__(8 * rows128_tl<BS>(), 4) void encode_rows128_kernel
     for (int i = 2; i < 16; ++i) m = fmaxf(m, fabsf(x[i]));
     uint32_t mb = group_max_bits<32>(o.valid ? __float_as_uint(m) : 0u);
     mb = max(mb, (uint32_t)__shfl_xor((int)mb, 32, 64));
-    if (lane == 0) red[r & 1][wave] = mb;
+    if (lane == 0) red[slot][wave] = mb;
     __syncthreads();
-    const uint32_t *rd = red[r & 1] + (wave & ~(GW - 1));
+    const uint32_t *rd = red[slot] + (wave & ~(GW - 1));
     mb = rd[0];
 #pragma unroll
     for (int k = 1; k < GW; ++k) mb = max(mb, rd[k]);
@@ -878,7 +881,10 @@ hipError_t launch_b_deploy(const Problem &pb, const float *src, const SideTab &c
                            uint8_t *codes, uint8_t *scales, hipStream_t st) {
   if (pb.b_rows == 1) return launch16<1, 1, BS, F32, 2>(pb, src, cf, codes, scales, st);
   constexpr int TL = rows128_tl<BS>();
-  const dim3 grid((unsigned)(((pb.np + 127) / 128) * ((pb.kp + TL - 1) / TL)), (unsigned)pb.batch);
+  // few workgroups: each tile's terms over several of them, which load it again
+  const int64_t tiles = ((pb.np + 127) / 128) * ((pb.kp + TL - 1) / TL);
+  const int64_t z = std::min<int64_t>(std::max<int64_t>(pb.ncu / (tiles * pb.batch), 1), pb.T);
+  const dim3 grid((unsigned)tiles, (unsigned)pb.batch, (unsigned)z);
   hipLaunchKernelGGL((encode_rows128_kernel<BS, F32>), grid, dim3(8 * TL), 0, st, src, pb, cf, codes, scales);
   return hipGetLastError();
 }

@@ -373,3 +373,22 @@ def test_exact_dot_takes_the_large_tiles(case):
     batch, M, K, N, block = case
     f = FMM("tstar", batch, M, K, N, 1, block, "pow2_ceil", exact_dot=True)
     assert fmm_products_kernel(f.plan) == "gemm_dq256x128_kernel 256x128"
+
+
+@pytest.mark.parametrize("bs,rule,bf16", [(128, "fp32_amax", True), (32, "pow2_ceil", False)])
+@pytest.mark.parametrize("batch", [70, 300])
+def test_weight_blocks_over_workgroups(batch, bs, rule, bf16):
+    """A tile's terms over seven workgroups (one product), three (70) and one
+    (300): the same codes and scales."""
+    import torch
+    import paper_2609_26077_amd as fm
+    from paper_2609_26077_amd.runner import FMM
+    flags = fm.FMM_FLAG_B_BLOCK128 | (fm.FMM_FLAG_B_BF16 if bf16 else 0)
+    g = torch.Generator(device="cuda").manual_seed(14)
+    A = torch.randn((batch, 34, 256), generator=g, device="cuda")
+    B = torch.randn((batch, 256, 70), generator=g, device="cuda")
+    whole, one = (FMM("tstar", b, 34, 256, 70, 1, bs, rule, flags=flags) for b in (batch, 1))
+    whole.encode(A, B)
+    for b in (0, batch // 2, batch - 1):
+        one.encode(A[b:b + 1], B[b:b + 1])
+        assert all(torch.equal(x[0], y[b]) for x, y in zip(one.operands(), whole.operands()))
