@@ -7,6 +7,7 @@
 namespace fmm {
 namespace dev {
 
+constexpr float kFltMax = 3.402823466e38f;
 constexpr float kE4m3Max = 448.0f;
 constexpr float kClamp = 1e-12f;  // fl32(1e-12): the block maximum is clamped from below
 
@@ -45,8 +46,11 @@ __device__ __forceinline__ Scale block_scale(float amax, int rule) {
   Scale sc;
   const float a = fmaxf(amax, kClamp);
   if (rule == RULE_FP32_AMAX) {
-    const float s = div_by(a, kE4m3Max, 1.0f / kE4m3Max);   // (= a / 448 for every significand of a, compared)
-    sc.div = s;
+    // (= a / 448 for every significand of a, compared; a combination of finite
+    // operands may overflow: its block's scale is then inf, whose finite values
+    // div_by takes to zeros of their signs and whose infinite ones to NaN, as x / s does)
+    const float s = a <= kFltMax ? div_by(a, kE4m3Max, 1.0f / kE4m3Max) : a;
+    sc.div = fminf(s, kFltMax);
     sc.inv = __fdiv_rn(1.0f, s);
     sc.mul = 1.0f;
     sc.stored = __float_as_uint(s);

@@ -376,10 +376,10 @@ def test_exact_dot_takes_the_large_tiles(case):
 
 
 @pytest.mark.parametrize("bs,rule,bf16", [(128, "fp32_amax", True), (32, "pow2_ceil", False)])
-@pytest.mark.parametrize("batch", [70, 300])
+@pytest.mark.parametrize("batch", [30, 70, 300])
 def test_weight_blocks_over_workgroups(batch, bs, rule, bf16):
-    """A tile's terms over seven workgroups (one product), three (70) and one
-    (300): the same codes and scales."""
+    """A tile's terms over seven workgroups (one product), fewer and one (300):
+    the same codes and scales."""
     import torch
     import paper_2609_26077_amd as fm
     from paper_2609_26077_amd.runner import FMM
@@ -392,3 +392,41 @@ def test_weight_blocks_over_workgroups(batch, bs, rule, bf16):
     for b in (0, batch // 2, batch - 1):
         one.encode(A[b:b + 1], B[b:b + 1])
         assert all(torch.equal(x[0], y[b]) for x, y in zip(one.operands(), whole.operands()))
+
+
+@pytest.mark.parametrize("depth,block,flags", [(1, 16, 0), (1, 128, 0), (2, 32, 0), (3, 32, 0), (1, 128, 2), (1, 32, 6)])
+def test_fp32_scales_of_overflowing_combinations(depth, block, flags):
+    """Finite operands whose combination overflows binary32: its block's scale
+    is infinite, its finite values' codes zeros, and every other block as if
+    the overflowing values were not there."""
+    import torch
+    from paper_2609_26077_amd.runner import FMM
+    n = 1 << depth
+    M, K, N = 160 * n, 384 * n, 160 * n
+    g = torch.Generator(device="cuda").manual_seed(15)
+    A = torch.randn((1, M, K), generator=g, device="cuda")
+    B = torch.randn((1, K, N), generator=g, device="cuda")
+    f = FMM("strassen", 1, M, K, N, depth, block, "fp32_amax", flags=flags)
+    f.encode(A, B)
+    plain = [t[0] for t in f.operands()]
+    # position (row 5, k 130) of every sub-block of A, (k 130, column 5) of B
+    A.view(n, 160, n, 384)[:, 5, :, 130] = 3e38
+    B.view(n, 384, n, 160)[:, 130, :, 5] = 3e38
+    f.encode(A, B)
+    rows = {0: slice(5, 6), 1: slice(0, 128) if flags & 2 else slice(5, 6)}
+    kb = 130 // block
+    for side in (0, 1):
+        codes, scales = (t[0] for t in f.operands()[2 * side:2 * side + 2])
+        pc, ps = plain[2 * side:2 * side + 2]
+        terms = torch.isinf(scales[:, 5, kb])
+        assert terms.any() and not torch.isnan(scales).any()
+        hit = torch.zeros_like(scales, dtype=torch.bool)
+        hit[:, rows[side], kb] = True
+        assert torch.equal(scales[~hit], ps[~hit])
+        wide = hit.repeat_interleave(block, dim=2)
+        assert torch.equal(codes[~wide], pc[~wide])
+        over = codes[terms][:, rows[side], kb * block:(kb + 1) * block].clone()
+        assert (scales[terms][:, rows[side], kb] == float("inf")).all()
+        assert (over[:, 5 - rows[side].start, 130 - kb * block] & 0x7F == 0x7E).all()
+        over[:, 5 - rows[side].start, 130 - kb * block] = 0
+        assert (over & 0x7F == 0).all()
