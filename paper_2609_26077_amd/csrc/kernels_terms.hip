@@ -33,8 +33,8 @@
 //           128 and 4.8e-7 in one accumulation, over 256 8.3e-8 either way.)
 //   PROMOTE fp32 scales: codes to bf16 at scale 1, each block's partial sum
 //           times sA sB (formed for the 32 x 32 tile by one
-//           v_mfma_f32_32x32x2_f32: sA in the first contracted position, zero
-//           in the second) into the fp32 accumulator
+//           v_mfma_f32_32x32x2_f32: sA and sB in the first contracted position,
+//           zeros in the second) into the fp32 accumulator
 #include <hip/hip_runtime.h>
 
 #include <cmath>
@@ -154,7 +154,7 @@ struct Side {
         if constexpr (MODE == PROMOTE) {
           const float *s = reinterpret_cast<const float *>(scale[i]) + kb0;
 #pragma unroll
-          for (int b = 0; b < NSC; ++b) f.sc[i][b] = b < nb ? __float_as_uint(s[b]) : 0u;
+          for (int b = 0; b < NSC; ++b) f.sc[i][b] = h == 0 && b < nb ? __float_as_uint(s[b]) : 0u;
         } else {
           // E8M0 bytes: MX those of the lane's own instruction halves, DQ (block 16: the
           // lane half's own) in the order of the instructions (127 = 1 past the end)
@@ -276,8 +276,8 @@ __global__ __launch_bounds__(kThreads, (TA * TB == 1 && MODE != PROMOTE ? 4 : 2)
                   for (int e = 0; e < 16; ++e) acc[i][j][e] = __fadd_rn(acc[i][j][e], part[i][j][e]);
                   continue;
                 }
-                const float x = h == 0 ? __uint_as_float(fa.sc[i][blk]) : 0.0f;
-                const v16f s2 = __builtin_amdgcn_mfma_f32_32x32x2f32(x, __uint_as_float(fb.sc[j][blk]), (v16f){}, 0, 0, 0);
+                const v16f s2 = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(fa.sc[i][blk]), __uint_as_float(fb.sc[j][blk]),
+                                                                     (v16f){}, 0, 0, 0);
 #pragma unroll
                 for (int e = 0; e < 16; ++e) acc[i][j][e] = __fmaf_rn(s2[e], part[i][j][e], acc[i][j][e]);
               }

@@ -430,3 +430,40 @@ def test_fp32_scales_of_overflowing_combinations(depth, block, flags):
         assert (over[:, 5 - rows[side].start, 130 - kb * block] & 0x7F == 0x7E).all()
         over[:, 5 - rows[side].start, 130 - kb * block] = 0
         assert (over & 0x7F == 0).all()
+
+
+@pytest.mark.parametrize("block", [16, 32, 128])
+@pytest.mark.parametrize("M,N", [(34, 38), (1538, 1474)])
+def test_rows_fp32_infinite_scales(block, M, N):
+    """An infinite scale of either side (a combination that overflowed) reaches
+    the elements of C that the definition's sums of sA sB times block products
+    give it: infinite where the sum is, NaN where an infinite product is of
+    zero or meets its opposite."""
+    import numpy as np
+    import torch
+    import paper_2609_26077_amd as fm
+    from paper_2609_26077_amd.runner import FMM
+    K = 2 * 3 * block
+    m, n = M // 2, N // 2
+    g = torch.Generator(device="cuda").manual_seed(16)
+    A = torch.randn((1, M, K), generator=g, device="cuda")
+    B = torch.randn((1, K, N), generator=g, device="cuda")
+    A.view(2, m, 2, K // 2)[:, 3, :, 5] = 3e38
+    B.view(2, K // 2, 2, n)[:, block + 2, :, 7] = 3e38
+    f = FMM("strassen", 1, M, K, N, 1, block, "fp32_amax")
+    C = f.matmul(A, B)[0]
+    ac, asc, bc, bsc = (t[0] for t in f.operands())
+    W = fm.fmm_realization_tables(f.real, 1)[2]
+    want = torch.zeros((M, N), device="cuda")
+    for r in range(7):
+        P = torch.zeros((m, n), device="cuda")
+        for k in range(3):
+            x = ac[r, :, k * block:(k + 1) * block].contiguous().view(torch.float8_e4m3fn).double()
+            y = bc[r, :, k * block:(k + 1) * block].contiguous().view(torch.float8_e4m3fn).double()
+            S = (asc[r, :, k][:, None] * bsc[r, :, k][None]).double()
+            P = (P.double() + S * (x @ y.T.contiguous())).float()        # one rounding, as a fused multiply-add
+        for q in np.flatnonzero(W[r]):
+            want[(q & 1) * m:(q & 1) * m + m, (q >> 1) * n:(q >> 1) * n + n] += float(W[r, q]) * P
+    assert torch.isinf(want).any() and torch.isnan(want).any()
+    for kind in (torch.isnan, torch.isposinf, torch.isneginf):
+        assert torch.equal(kind(C), kind(want))
