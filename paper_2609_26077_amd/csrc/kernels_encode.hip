@@ -1132,17 +1132,18 @@ hipError_t launch_pair_any(const Problem &pb, PairArgs &g, hipStream_t st) {
 // flight, so A's tile count decides. Blocks 16 and 32, up to 4608 (A of M x K,
 // its tiles): 3132x4928 (3920) 33.0 / 30.2, 4096x5632 (5630) 37.3 / 39.3, 7180x4672
 // (8530) 57.6 / 64.2, 343 of 1636x64 (35300) 114 / 165; block 128, two of whose
-// workgroups fill a CU, up to 1152: 6226x512 (780) 15.0 / 12.8, 4 of 4348x256 (1090)
-// 20.8 / 15.4, 3090x2304 (1750) 18.8 / 20.9, 7 of 1024x1024 (1790) 17.9 / 20.7, 113
+// workgroups fill a CU, up to 1280: 6226x512 (780) 15.0 / 12.8, 4 of 4348x256 (1090)
+// 20.8 / 15.4, 3084x1536 (1160) 18.1 / 16.1, 3090x2304 (1750) 18.8 / 20.9, 7 of 1024x1024 (1790) 17.9 / 20.7, 113
 // of 110x512 (1580) 16.9 / 27.5, 5734x3328 (4670) 31.0 / 38.8. Many bytes gain nothing
 // (whole tiles counted): 302 MB 87.9 / 91.9, 537 MB 143 / 154 (block 32), 134 MB
 // 59.4 / 61.6, 497 of 20x256 by 256x90 (81 MB) 31.0 / 37.9 (block 128).
-// Depth 2, whose sides have one workgroup size by themselves: to 1 GiB (8192^3 286
-// / 274, 1024^3 19.1 / 10.6, 180 of 768^3 393 / 348, 270 of 512x512x1024 429 / 370;
-// past it 99 of 1024x2048x1024 736 / 804, 220 of 528x2048x300 777 / 813) but for
-// large batches of products of 1 to 2 MiB (190 of 512^3 186 / 199, 405 372 / 412, 810
-// of 256x512x256 358 / 387; 71 of 512^3 73 / 63, 324 of 640x512x640 356 / 356, 1621 of
-// 256^3 404 / 370).
+// Depth 2, whose sides have one workgroup size by themselves: always (8192^3 286 /
+// 274, 1024^3 19.1 / 10.6, 180 of 768^3 393 / 348, 404 of 1024x512x1024 1056 / 969, 38 of
+// 636x3392x4028 1836 / 1699) but for large batches of products of 1 to 2 MiB (190 of
+// 512^3 186 / 199, 405 372 / 412, 810 of 256x512x256 358 / 387; 71 of 512^3 73 / 63, 324 of
+// 640x512x640 356 / 356, 1621 of 256^3 404 / 370) and, past 1 GiB, of some 6 to 18 (99 of
+// 1024x2048x1024 736 / 804, 220 of 528x2048x300 777 / 813, 266 of 1288x1664x224 1739 /
+// 1813; 203 of 1024x512x2048, 6 MiB, 881 / 782, 137 of 1368x1536x2104, 20, 1695 / 1582).
 // Other shapes, on the sixteen-wave tiles over up to 16 blocks: always where
 // both sides stage them anyway (more than 8 blocks; <3,3,3;27> 5 MB 14.0 / 8.1,
 // 302 MB 186 / 180). Smaller grids trade their wider depth-1 tiles for it:
@@ -1168,12 +1169,13 @@ bool one_launch(const Problem &pb) {
   if (pb.depth == 2) {
     // (1024 threads a tile of at least 8 rows x 64 positions, fewer than 2^32 on the axis)
     if ((up(pb.mp, 8) + up(pb.np, 8)) / 8 * (up(pb.kp, 64) / 64) >= int64_t(1) << 22) return false;
-    return bytes <= 256 * MiB || ((each < MiB || each > 9 * MiB / 4) && bytes <= 1024 * MiB);
+    return !(bytes > 256 * MiB && each >= MiB && each <= 9 * MiB / 4) &&
+           !(bytes > 1024 * MiB && each >= 25 * MiB / 4 && each <= 18 * MiB);
   }
   using TA = Tile<1, 16, 0>;
   const int64_t a = pb.batch * up(pb.mp, TA::TR) * up(pb.kp, TA::TL);       // positions of A's tiles
   const int64_t b = pb.batch * up(pb.np, kB1Rows) * up(pb.kp, wide ? 128 : 64);
-  return a <= (wide ? 1152 : 4608) * TA::TR * TA::TL && 16 * (a + b) <= (wide ? 64 : 192) * MiB;
+  return a <= (wide ? 1280 : 4608) * TA::TR * TA::TL && 16 * (a + b) <= (wide ? 64 : 192) * MiB;
 }
 
 }  // namespace

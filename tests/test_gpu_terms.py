@@ -268,7 +268,8 @@ def test_more_workgroups_than_one_launch_takes():
     # (depth, block, rule, batch, M, K, N, cubic shape): batches past a bound on the
     # shared encode launch, whose products alone are within it
     (2, 32, "pow2_ceil", 140, 512, 512, 512, None),        # 256 MiB of 2 MiB products at depth 2
-    (1, 128, "fp32_amax", 73, 124, 512, 36, None),         # 1152 of A's tiles at block 128 (1168)
+    (2, 128, "fp32_amax", 65, 1024, 2048, 1024, None),     # 1 GiB of 16 MiB products
+    (1, 128, "fp32_amax", 81, 124, 512, 36, None),         # 1280 of A's tiles at block 128 (1296)
     (1, 32, "pow2_ceil", 700, 100, 64, 18, None),          # 4608 of them at blocks 16 and 32 (4900)
     (1, 128, "pow2_ocp", 7, 768, 768, 768, (3, 1, 3)),     # 1024 tiles where a side has fewer than four blocks
     (1, 16, "fp32_amax", 15, 256, 512, 1024, (1, 2, 4)),   # 1792 of them at blocks 16 and 32
