@@ -1031,19 +1031,25 @@ hipError_t launch_noise_side(const Problem &pb, const float *src, const SideTab 
   return hipErrorInvalidValue;
 }
 
-// out[(bt * 2 + side) * T + r][q]: one workgroup per (term, side, product)
-// sums the term's slots, thread t taking slots t, t + 256, .. in that order,
-// then the lanes by a fixed butterfly and the four waves in order.  (A thread
-// per output walking every slot, and a pass that cleared the slots nobody
-// writes, took 448 us for two 2048 x 1024 x 1536 products; this takes 3.8.)
-__global__ __launch_bounds__(256) void noise_reduce_kernel(NoiseSide a, NoiseSide b, double *__restrict__ out, int64_t T) {
-  const int t = threadIdx.x;
-  const int64_t r = blockIdx.x, side = blockIdx.y, bt = blockIdx.z;
+// out[(bt * 2 + side) * T + r][q]: W waves of a workgroup per (term, side,
+// product) sum the term's slots, thread t taking slots t, t + 64 W, .. in that
+// order, then the lanes by a fixed butterfly and the waves in order.  Four waves,
+// or one where no term has more than 256 slots.  (A thread per output walking
+// every slot, and a pass that cleared the slots nobody writes, took 448 us for two
+// 2048 x 1024 x 1536 products, four waves 3.8; the whole measurement of 1000
+// products of 64^3 57 us, 64 with four waves for a few slots each, 52 with one.)
+template <int W>
+__global__ __launch_bounds__(256) void noise_reduce_kernel(NoiseSide a, NoiseSide b, double *__restrict__ out, int64_t T,
+                                                           int64_t total) {
+  const int t = threadIdx.x % (64 * W), part = threadIdx.x / (64 * W);
+  const int64_t i = (int64_t)blockIdx.x * (4 / W) + part;      // (bt, side, r); uniform over a wave
+  if (i >= total) return;                                      // (W = 4: never)
+  const int64_t r = i % T, side = i / T % 2, bt = i / T / 2;
   const NoiseSide s = side == 0 ? a : b;
   const int w0 = s.wpt * (int)(r % s.step);
   const int64_t n = s.tiles * s.wpt;
   double e2 = 0.0, x2 = 0.0;
-  for (int64_t k = t; k < n; k += 256) {
+  for (int64_t k = t; k < n; k += 64 * W) {
     const int64_t tile = k / s.wpt;
     const int64_t slot = ((bt * s.tiles + tile) * s.waves + w0 + (k - tile * s.wpt)) * T + r;
     e2 += s.partial[2 * slot];
@@ -1054,16 +1060,23 @@ __global__ __launch_bounds__(256) void noise_reduce_kernel(NoiseSide a, NoiseSid
     e2 += __shfl_xor(e2, sh, 64);
     x2 += __shfl_xor(x2, sh, 64);
   }
-  __shared__ double se[4], sx[4];
-  if ((t & 63) == 0) {
-    se[t >> 6] = e2;
-    sx[t >> 6] = x2;
-  }
-  __syncthreads();
-  if (t == 0) {
-    double *o = out + ((bt * 2 + side) * T + r) * 2;
-    o[0] = ((se[0] + se[1]) + se[2]) + se[3];
-    o[1] = ((sx[0] + sx[1]) + sx[2]) + sx[3];
+  double *o = out + 2 * i;
+  if constexpr (W == 1) {
+    if (t == 0) {
+      o[0] = e2;
+      o[1] = x2;
+    }
+  } else {
+    __shared__ double se[4], sx[4];
+    if ((t & 63) == 0) {
+      se[t >> 6] = e2;
+      sx[t >> 6] = x2;
+    }
+    __syncthreads();
+    if (t == 0) {
+      o[0] = ((se[0] + se[1]) + se[2]) + se[3];
+      o[1] = ((sx[0] + sx[1]) + sx[2]) + sx[3];
+    }
   }
 }
 
@@ -1091,8 +1104,12 @@ int launch_encode_noise(const Problem &pb, const DeviceTables &tab, const float 
                       : launch_noise_side<1, 2>(pb, B, b_tab(tab), ws + wl.b_codes, ws + wl.b_scales, pbp, st);
     if (e != hipSuccess) return e;
   }
-  hipLaunchKernelGGL(noise_reduce_kernel, dim3((unsigned)pb.T, 2, (unsigned)pb.batch), dim3(256), 0, st,
-                     noise_side<0>(pb, pa), noise_side<1>(pb, pbp), out, pb.T);
+  const NoiseSide na = noise_side<0>(pb, pa), nb = noise_side<1>(pb, pbp);
+  const int64_t total = pb.batch * 2 * pb.T;
+  if (std::max(na.tiles * na.wpt, nb.tiles * nb.wpt) <= 256)
+    hipLaunchKernelGGL(noise_reduce_kernel<1>, dim3((unsigned)((total + 3) / 4)), dim3(256), 0, st, na, nb, out, pb.T, total);
+  else
+    hipLaunchKernelGGL(noise_reduce_kernel<4>, dim3((unsigned)total), dim3(256), 0, st, na, nb, out, pb.T, total);
   return hipGetLastError();
 }
 

@@ -44,3 +44,12 @@ def test_noise_partials(case):
     for i in range(b):
         o = oracle_noise(A[i], B[i], "strassen", depth, bs, 1)
         assert np.allclose(g[i], o, rtol=1e-12, atol=0)
+
+
+def test_noise_of_many_small_products():
+    """65 products of a few partials a term (one wave an output, the last
+    workgroup partly idle): against the oracle."""
+    b, M, K, N, bs = 65, 34, 64, 38, 32
+    A, B, _, _, _, g = gpu_noise("strassen", "gaussian", b, M, K, N, 1, bs, 1)
+    for i in (0, 31, 64):
+        assert np.allclose(g[i], oracle_noise(A[i], B[i], "strassen", 1, bs, 1), rtol=1e-12, atol=0)
