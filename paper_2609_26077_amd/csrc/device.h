@@ -103,5 +103,30 @@ __device__ __forceinline__ uint32_t e4m3_pack4_pow2(float v0, float v1, float v2
   return __builtin_bit_cast(uint32_t, w);
 }
 
+typedef __bf16 v8bf __attribute__((ext_vector_type(8)));
+
+// Eight codes (two little-endian words) -> their values times the power of two
+// whose exponent field `s` carries, as bf16 (exact).
+__device__ __forceinline__ v8bf dequant8(uint32_t lo, uint32_t hi, float s) {
+  typedef __bf16 v2bf __attribute__((ext_vector_type(2)));
+  const v2bf a = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8((int)lo, s, false);
+  const v2bf b = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8((int)lo, s, true);
+  const v2bf c = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8((int)hi, s, false);
+  const v2bf d = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8((int)hi, s, true);
+  v8bf r;
+  r[0] = a[0]; r[1] = a[1]; r[2] = b[0]; r[3] = b[1];
+  r[4] = c[0]; r[5] = c[1]; r[6] = d[0]; r[7] = d[1];
+  return r;
+}
+
+// A float whose exponent field is E8M0 byte i of word w, as the scale operand
+// of v_cvt_scalef32_pk_bf16_fp8, which reads the exponent field alone (its sign
+// and mantissa bits, here parts of the neighbouring bytes, leave the result
+// unchanged: every code at every exponent -48 .. 120 measured), so one shift
+// places the byte.
+__device__ __forceinline__ float e8m0_at(uint32_t w, int i) {
+  return __uint_as_float(i == 3 ? w >> 1 : w << (23 - 8 * i));
+}
+
 }  // namespace dev
 }  // namespace fmm

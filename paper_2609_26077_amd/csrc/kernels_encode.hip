@@ -31,7 +31,8 @@ namespace {
 
 // One operand side's coefficient tables: the nonzero entries of every term in
 // ascending block order (offsets, entries; read at depth 1) and the dense
-// flattened rows, T x 4^l fp32 with zeros (read at depths 2 and 3).
+// flattened rows, T x 4^l fp32 with zeros (read at depths 2 and 3, and at depth 1
+// by the weight-block encoder).
 struct SideTab {
   const int32_t *off;
   const CoefEntry *ent;
@@ -491,7 +492,8 @@ __global__ __launch_bounds__((Tile<DEPTH, 16, SIDE, narrow_b(SIDE, DEPTH, BS, MO
 // that read a few megabytes each; in one launch the sides run side by side
 // (us, separate / one launch: 256^3 11.8 / 8.0, 1024^3 11.9 / 7.8, 100 of
 // 256^3 22.8 / 20.7, 4096^3 45.9 / 43.1; depth 2 1024^3 19.1 / 10.6, 4096^3
-// 71.5 / 62.5, 8192^3 286 / 274).  Both sides then have one workgroup size:
+// 71.5 / 62.5, 8192^3 286 / 274; one_launch has where it pays).  Both sides then
+// have one workgroup size:
 // at depth 1 256 threads (A's four waves each take every fourth term; B on
 // the narrow tile) at blocks 16 and 32, 512 at block 128; at depth 2 1024, as
 // each has by itself.  Alternating the sides' workgroups: up to 9% slower.
@@ -545,8 +547,8 @@ __device__ __forceinline__ uint32_t group_max_bits(uint32_t m) {
 }
 
 // Scale and codes of a lane's 4 values of a block whose maximum is m: the
-// fp32 rule divides (IEEE), the power-of-two rules scale exactly inside the
-// conversion.
+// fp32 rule rounds the quotient to nearest (div_by), the power-of-two rules scale
+// exactly inside the conversion.
 template <bool F32>
 __device__ __forceinline__ uint32_t quantize4(const Problem &pb, float m, float x0, float x1, float x2, float x3,
                                               uint32_t &stored) {

@@ -27,8 +27,10 @@
 // holds row r, elements [8h, 8h+8); 23 retained bits), so the products of the
 // dequantized operands are accumulated in fp32.
 //
-// Products with few tiles, and the other exact-dot plans in the row layout,
-// run on gemm_terms_kernel (one wave per inner term).
+// Row layout: fp8 plans on gemm_mx_kernel, exact-dot and fp32-scale plans at block
+// 128 on gemm_promote_kernel, where their 128 x 128 tiles are the faster ones; the
+// others, and tiled products with few tiles, on gemm_terms_kernel (one wave per inner
+// term).  terms_edge decides.
 //
 // Output layout of the 32x32 instructions: lane l, register j holds
 // column l % 32, row 8 (j / 4) + 4 (l / 32) + j % 4.
@@ -46,20 +48,9 @@ namespace {
 
 typedef int v8i __attribute__((ext_vector_type(8)));
 typedef float v16f __attribute__((ext_vector_type(16)));
-typedef __bf16 v8bf __attribute__((ext_vector_type(8)));
-typedef __bf16 v2bf __attribute__((ext_vector_type(2)));
-
-// eight e4m3 codes (little-endian in two words) -> eight bf16, exactly
-__device__ __forceinline__ v8bf codes_bf16(uint2 w) {
-  const v2bf a = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8((int)w.x, 1.0f, false);
-  const v2bf b = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8((int)w.x, 1.0f, true);
-  const v2bf c = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8((int)w.y, 1.0f, false);
-  const v2bf d = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8((int)w.y, 1.0f, true);
-  v8bf r;
-  r[0] = a[0]; r[1] = a[1]; r[2] = b[0]; r[3] = b[1];
-  r[4] = c[0]; r[5] = c[1]; r[6] = d[0]; r[7] = d[1];
-  return r;
-}
+using dev::dequant8;
+using dev::e8m0_at;
+using dev::v8bf;
 
 constexpr int BM = 128, BN = 128, BK = 128;
 constexpr int kThreads = 256;
@@ -280,28 +271,6 @@ constexpr int kSlots = 4;
 using dma::copy16;
 using dma::copy4;
 using dma::wait_vmcnt;
-
-// codes in dwords d, d + 1 of a fragment, times the power of two whose
-// exponent field `s` carries, as eight bf16 (exact: the dequantized values)
-__device__ __forceinline__ v8bf dequant8(const v8i &f, int d, float s) {
-  const v2bf a = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(f[d], s, false);
-  const v2bf b = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(f[d], s, true);
-  const v2bf c = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(f[d + 1], s, false);
-  const v2bf e = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(f[d + 1], s, true);
-  v8bf r;
-  r[0] = a[0]; r[1] = a[1]; r[2] = b[0]; r[3] = b[1];
-  r[4] = c[0]; r[5] = c[1]; r[6] = e[0]; r[7] = e[1];
-  return r;
-}
-
-// A float whose exponent field is byte i of a scale record, as the scale
-// operand of v_cvt_scalef32_pk_bf16_fp8, which reads the exponent field alone
-// (its sign and mantissa bits, here parts of the neighbouring bytes, leave
-// the result unchanged: every code at every exponent -48 .. 120 measured), so
-// one shift places the byte
-__device__ __forceinline__ float e8m0_at(int w, int i) {
-  return __uint_as_float(i == 3 ? (uint32_t)w >> 1 : (uint32_t)w << (23 - 8 * i));
-}
 
 // ---------------------------------------------------------------------------
 // Fused sub-products on the 128 x 128 tile layout (E8M0 scales), two waves per
@@ -544,10 +513,10 @@ __global__ __launch_bounds__(kTileThreads, 1) void gemm_tile128_kernel(GemmArgs 
     for (int tt = 0; tt < 4; ++tt) {
       const int c = tt >> 1, d = 4 * c + 2 * (tt & 1);
       const int sbyte = BS == 16 ? 2 * SS + c : BS == 32 ? 2 * c + SS : 0;
-      const v8bf fb = dequant8(f.b, d, e8m0_at(sb, sbyte));
+      const v8bf fb = dequant8(f.b[d], f.b[d + 1], e8m0_at(sb, sbyte));
 #pragma unroll
       for (int i = 0; i < 2; ++i) {
-        const v8bf fa = dequant8(f.a[i], d, e8m0_at(sa[i], sbyte));
+        const v8bf fa = dequant8(f.a[i][d], f.a[i][d + 1], e8m0_at(sa[i], sbyte));
         acc[i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa, fb, acc[i], 0, 0, 0);
       }
     }
@@ -728,8 +697,10 @@ __global__ __launch_bounds__(kThreads, 1) void gemm_promote_kernel(GemmArgs g) {
 #pragma unroll
       for (int i = 0; i < 2; ++i) {
         const int rowa = wm * 64 + 32 * i + r32, rowb = wn * 64 + 32 * i + r32;
-        fa[i] = codes_bf16(*reinterpret_cast<const uint2 *>(la + swz(rowa, c) + 8 * h));
-        fb[i] = codes_bf16(*reinterpret_cast<const uint2 *>(lb + swz(rowb, c) + 8 * h));
+        const uint2 wa = *reinterpret_cast<const uint2 *>(la + swz(rowa, c) + 8 * h);
+        fa[i] = dequant8(wa.x, wa.y, 1.0f);
+        const uint2 wb = *reinterpret_cast<const uint2 *>(lb + swz(rowb, c) + 8 * h);
+        fb[i] = dequant8(wb.x, wb.y, 1.0f);
       }
 #pragma unroll
       for (int i = 0; i < 2; ++i)

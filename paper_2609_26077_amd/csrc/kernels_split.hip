@@ -275,28 +275,9 @@ constexpr int kSlot = kCodeA + kCodeB + kScaleA + kScaleB;  // 26112 B
 static_assert(2 * kSlots * kSlot <= 160 * 1024, "two workgroups per CU");
 }  // namespace dq
 
-typedef __bf16 v8bfq __attribute__((ext_vector_type(8)));
-typedef __bf16 v2bfq __attribute__((ext_vector_type(2)));
-
-// eight codes (two little-endian words) -> their values times the power of
-// two whose exponent field `s` carries, as bf16 (exact)
-__device__ __forceinline__ v8bfq dequant8(uint32_t lo, uint32_t hi, float s) {
-  const v2bfq a = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8((int)lo, s, false);
-  const v2bfq b = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8((int)lo, s, true);
-  const v2bfq c = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8((int)hi, s, false);
-  const v2bfq d = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8((int)hi, s, true);
-  v8bfq r;
-  r[0] = a[0]; r[1] = a[1]; r[2] = b[0]; r[3] = b[1];
-  r[4] = c[0]; r[5] = c[1]; r[6] = d[0]; r[7] = d[1];
-  return r;
-}
-
-// A float whose exponent field is E8M0 byte i of word w, as the scale operand
-// of v_cvt_scalef32_pk_bf16_fp8, which reads the exponent field alone (the
-// neighbouring bytes in its sign and mantissa bits do not change the result)
-__device__ __forceinline__ float e8m0_byte(uint32_t w, int i) {
-  return __uint_as_float(i == 3 ? w >> 1 : w << (23 - 8 * i));
-}
+using dev::dequant8;
+using dev::e8m0_at;
+using dev::v8bf;
 
 template <int BS>
 __global__ __launch_bounds__(kThreads, 2) void gemm_dq256x128_kernel(SplitArgs g) {
@@ -379,13 +360,13 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_dq256x128_kernel(SplitArgs g
         rb[j] = *reinterpret_cast<const uint4 *>(lb + swz64(wn * 64 + 32 * j + r32, 2 * c + h));
 #pragma unroll
       for (int u = 0; u < 2; ++u) {
-        v8bfq fa[4], fb[2];
+        v8bf fa[4], fb[2];
 #pragma unroll
         for (int i = 0; i < 4; ++i)
-          fa[i] = u == 0 ? dequant8(ra[i].x, ra[i].y, e8m0_byte(wa, i)) : dequant8(ra[i].z, ra[i].w, e8m0_byte(wa, i));
+          fa[i] = u == 0 ? dequant8(ra[i].x, ra[i].y, e8m0_at(wa, i)) : dequant8(ra[i].z, ra[i].w, e8m0_at(wa, i));
 #pragma unroll
         for (int j = 0; j < 2; ++j)
-          fb[j] = u == 0 ? dequant8(rb[j].x, rb[j].y, e8m0_byte(wb, j)) : dequant8(rb[j].z, rb[j].w, e8m0_byte(wb, j));
+          fb[j] = u == 0 ? dequant8(rb[j].x, rb[j].y, e8m0_at(wb, j)) : dequant8(rb[j].z, rb[j].w, e8m0_at(wb, j));
 #pragma unroll
         for (int i = 0; i < 4; ++i)
 #pragma unroll
@@ -471,18 +452,7 @@ struct Geo {
 }  // namespace ex
 
 // eight e4m3 codes (little-endian in two words) -> eight bf16, exactly
-typedef __bf16 v8bfx __attribute__((ext_vector_type(8)));
-typedef __bf16 v2bfx __attribute__((ext_vector_type(2)));
-__device__ __forceinline__ v8bfx codes8_to_bf16(uint32_t lo, uint32_t hi) {
-  const v2bfx a = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8((int)lo, 1.0f, false);
-  const v2bfx b = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8((int)lo, 1.0f, true);
-  const v2bfx c = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8((int)hi, 1.0f, false);
-  const v2bfx d = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8((int)hi, 1.0f, true);
-  v8bfx r;
-  r[0] = a[0]; r[1] = a[1]; r[2] = b[0]; r[3] = b[1];
-  r[4] = c[0]; r[5] = c[1]; r[6] = d[0]; r[7] = d[1];
-  return r;
-}
+__device__ __forceinline__ v8bf codes8_to_bf16(uint32_t lo, uint32_t hi) { return dequant8(lo, hi, 1.0f); }
 
 template <int BS>
 __global__ __launch_bounds__(ex::kThreadsX, 2) void gemm_exact128x128_kernel(SplitArgs g) {
@@ -569,7 +539,7 @@ __global__ __launch_bounds__(ex::kThreadsX, 2) void gemm_exact128x128_kernel(Spl
   // inline constant: no register clears) and is preceded by the previous
   // block's promote.  FRESH: the step opens a block of 128.  prev: the
   // previous step's slot.
-  auto mfma_group = [&](const v8bfx (&a)[2], const v8bfx (&b)[2], bool opens) {
+  auto mfma_group = [&](const v8bf (&a)[2], const v8bf (&b)[2], bool opens) {
 #pragma unroll
     for (int i = 0; i < 2; ++i)
 #pragma unroll
@@ -582,7 +552,7 @@ __global__ __launch_bounds__(ex::kThreadsX, 2) void gemm_exact128x128_kernel(Spl
     if (BS == 16) {
 #pragma unroll
       for (int blk = 0; blk < 4; ++blk) {
-        v8bfx a[2], b[2];
+        v8bf a[2], b[2];
 #pragma unroll
         for (int i = 0; i < 2; ++i) {
           const uint2 w = *reinterpret_cast<const uint2 *>(la + swz64(wm * 64 + 32 * i + r32, blk) + 8 * h);
@@ -610,7 +580,7 @@ __global__ __launch_bounds__(ex::kThreadsX, 2) void gemm_exact128x128_kernel(Spl
 #pragma unroll
         for (int tt = 0; tt < 2; ++tt) {
           const bool opens = BS == 32 ? tt == 0 : (fresh && half == 0 && tt == 0);
-          v8bfx a[2], b[2];
+          v8bf a[2], b[2];
 #pragma unroll
           for (int i = 0; i < 2; ++i) a[i] = tt == 0 ? codes8_to_bf16(fa[i].x, fa[i].y) : codes8_to_bf16(fa[i].z, fa[i].w);
 #pragma unroll
@@ -627,9 +597,9 @@ __global__ __launch_bounds__(ex::kThreadsX, 2) void gemm_exact128x128_kernel(Spl
     }
   };
 
-  // Step s: wait for this wave's own transfers of step s (four a step; those
-  // of step s + 1 may stay in flight), barrier, start step s + 2 into the
-  // slot of step s - 2, multiply step s.
+  // Step s: wait for this wave's own transfers of step s (five a step, four of
+  // codes and one of scales; those of step s + 1 may stay in flight), barrier,
+  // start step s + 2 into the slot of step s - 2, multiply step s.
   auto slot_of = [&](int step) { return lds + (step & (ex::kSlotsX - 1)) * G::kSlot; };
   auto begin_step = [&](int step) -> const uint8_t * {
     if (step + 1 < nk) dma::wait_vmcnt<5>(); else dma::wait_vmcnt<0>();

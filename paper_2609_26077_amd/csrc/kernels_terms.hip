@@ -21,6 +21,7 @@
 //   MX      E8M0 scales, blocks 32 and 128: v_mfma_scale_f32_32x32x64_f8f6f4
 //   DQ      E8M0 scales, exact-dot flag or block 16: each code converted to
 //           bf16 with its block's power of two, v_mfma_f32_32x32x16_bf16.
+//           (The tiled 64-edge forms spill 8 to 10 of their 256 registers.)
 //           The exponents enter one lower on both sides (so that no code
 //           overflows at the largest scale, 2^120) and P_r is multiplied by 4.
 //           In the tiled layout the instructions accumulate over the whole
@@ -48,8 +49,9 @@ namespace {
 
 typedef int v8i __attribute__((ext_vector_type(8)));
 typedef float v16f __attribute__((ext_vector_type(16)));
-typedef __bf16 v8bf __attribute__((ext_vector_type(8)));
-typedef __bf16 v2bf __attribute__((ext_vector_type(2)));
+using dev::dequant8;
+using dev::e8m0_at;
+using dev::v8bf;
 
 enum { MX = 0, DQ = 1, PROMOTE = 2 };
 
@@ -64,21 +66,6 @@ struct TermArgs {
   int64_t first;                    // this launch's first (product, outer term, tile) item
   int R, depth, tiles_m, tiles_n;
 };
-
-// eight codes (two words) -> eight bf16, times the power of two in s's exponent field
-__device__ __forceinline__ v8bf dequant8(int lo, int hi, float s) {
-  const v2bf a = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(lo, s, false);
-  const v2bf b = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(lo, s, true);
-  const v2bf c = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(hi, s, false);
-  const v2bf d = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(hi, s, true);
-  v8bf r;
-  r[0] = a[0]; r[1] = a[1]; r[2] = b[0]; r[3] = b[1];
-  r[4] = c[0]; r[5] = c[1]; r[6] = d[0]; r[7] = d[1];
-  return r;
-}
-__device__ __forceinline__ float e8m0_at(uint32_t w, int i) {
-  return __uint_as_float(i == 3 ? w >> 1 : w << (23 - 8 * i));
-}
 
 // One side's operand of one wave: NT row tiles of 32 rows.
 template <int LAYOUT, int MODE, int BS, int NT>

@@ -137,8 +137,8 @@ int fmm_plan_create(const fmm_real *d, const fmm_plan_desc *desc, fmm_plan **out
 
   // large-tile path: one or two levels, 256-row tiles, whole 64-byte (blocks
   // 16, 32) or 128-byte (block 128) K steps; E8M0 scales at blocks 32 and 128
-  // on the fp8 matrix cores or (exact-dot flag) the folded-scale bf16 kernel,
-  // fp32 scales and block 16 on the promote kernel.  It writes every P_r (4
+  // on the fp8 matrix cores or (exact-dot flag, block 16) the folded-scale bf16
+  // kernel, fp32 scales on the kernel that promotes each block.  It writes every P_r (4
   // bytes per output of each term) and reads it back, 8 / k' bytes per flop
   // against the fused path's none: plans with a fused kernel take it by
   // default where that round trip costs less than the fused path's smaller
@@ -262,7 +262,7 @@ int fmm_plan_create(const fmm_real *d, const fmm_plan_desc *desc, fmm_plan **out
   const size_t s_wi = align256(wbase.size() * sizeof(float));   // zero-padded to 8 x 4
   const size_t s_wo = align256(std::max<size_t>(1, wouter.size()) * sizeof(float));
   const size_t s_wf = align256(std::max<size_t>(1, wfull.size()) * sizeof(float));
-  const size_t s_ud = align256(std::max<size_t>(1, U.size()) * sizeof(float));   // dense rows (the encoder at depths 2, 3)
+  const size_t s_ud = align256(std::max<size_t>(1, U.size()) * sizeof(float));   // dense rows (the encoder at depths 2 and 3, weight blocks at depth 1)
   const size_t s_vd = align256(std::max<size_t>(1, V.size()) * sizeof(float));
   const size_t o_ud = s_aoff + s_boff + s_aent + s_bent + s_wi + s_wo + s_wf;
   const size_t tot = o_ud + s_ud + s_vd;
