@@ -1166,9 +1166,11 @@ hipError_t launch_pair_any(const Problem &pb, PairArgs &g, hipStream_t st) {
 // Other shapes, on the sixteen-wave tiles over up to 16 blocks: always where
 // both sides stage them anyway (more than 8 blocks; <3,3,3;27> 5 MB 14.0 / 8.1,
 // 302 MB 186 / 180). Smaller grids trade their wider depth-1 tiles for it:
-// with four blocks and more a side up to 128 MiB, at block 128 32 (<2,2,3;11>
-// block 32: 21 MB 24.4 / 15.6, 105 MB 49.8 / 50.3, 154 MB 63.9 / 69.0; block 128:
-// 21 MB 23.7 / 17.3, 37 MB 24.2 / 21.9, 86 MB 45.1 / 52.1); with fewer, of which a tile
+// with four blocks and more a side up to 128 MiB, at block 128 32, an A of four
+// blocks beyond 24 only beside a B as large (<2,2,3;11> block 32, A + B: 8 + 13 MB
+// 24.4 / 15.6, 24 + 177 90.2 / 85.1, 38 + 113 65.1 / 63.8, 38 + 14 25.4 / 27.5,
+// 88 + 33 52.2 / 60.0, 88 + 66 63.9 / 69.0; block 128: 21 MB 23.7 / 17.3, 37 MB
+// 24.2 / 21.9, 86 MB 45.1 / 52.1); with fewer, of which a tile
 // holds little, by their tiles of 1024 positions per block, up to 1792, at block 128
 // 768 (block 32: <3,1,3;9> 1660 tiles 14.6 / 15.0, 2560 18.5 / 21.3, 5250 32.2 / 42.3,
 // <1,2,4;8> 1030 14.2 / 10.5, 6900 37.5 / 54.4; block 128: <3,1,3;9> 1030 13.3 / 9.8,
@@ -1183,7 +1185,8 @@ bool one_launch(const Problem &pb) {
     const int na = pb.gm * pb.gk, nb = pb.gk * pb.gn;
     if (na > 16 || nb > 16) return false;
     if (na < 4 || nb < 4) return pb.batch * pb.kp * (pb.mp + pb.np) <= (wide ? 768 : 1792) * 1024;
-    return (na > 8 && nb > 8) || bytes <= (wide ? 32 : 128) * MiB;
+    const int64_t a = 4 * pb.batch * pb.M * pb.K;
+    return (na > 8 && nb > 8) || (bytes <= (wide ? 32 : 128) * MiB && (na > 4 || a <= 24 * MiB || 2 * a <= bytes));
   }
   if (pb.depth == 2) {
     // (1024 threads a tile of at least 8 rows x 64 positions, fewer than 2^32 on the axis)
