@@ -109,12 +109,12 @@ enum {
    * encoded weights).  Depth 1 only. */
   FMM_FLAG_B_BF16 = 4,
   /* Take the large-tile sub-product path (FMM_LAYOUT_TILE256x64) whenever
-   * the shape allows it.  Without the flag, plans on the fp8 matrix cores
-   * take that path only where K / 2^l >= 1024, and at depth 1 not where the
-   * product's 128 x 128 tiles fill the chip and K / 2 is at most about 2048: it
-   * writes every fp32 P_r to the workspace and reads it back, which costs more
-   * than it saves there (plans with fp32 scales take it whenever the shape
-   * allows).  No effect on the result's definition; shapes the path cannot
+   * the shape allows it.  Without the flag, plans with E8M0 scales take that
+   * path only where K / 2^l >= 1024, and at depth 1 not where the fused
+   * 128 x 128 tiles are estimated the faster (fused_beats_large_tiles in
+   * plan.cpp): it writes every fp32 P_r to the workspace and reads it back,
+   * which costs more than it saves there (plans with fp32 scales take it
+   * whenever the shape allows).  No effect on the result's definition; shapes the path cannot
    * take ignore the flag. */
   FMM_FLAG_LARGE_TILE = 8
 };
